@@ -248,6 +248,17 @@ def test_turbo_codebook_matches_oracle():
         assert np.all(tab[b - 1, 1, L:] == 0)
 
 
+@pytest.mark.parametrize("b", [4, 5, 6, 7, 8])
+def test_turbo_codebook_cells_hold_one_threshold(b):
+    # the quantizer looks a coordinate's code up in cells of width 2^-(b-2):
+    # no cell may hold two positive thresholds, and all lie inside the table
+    tab = rq.rq_turbo_codebook()
+    th = tab[b - 1, 0, 1 << (b - 1):(1 << b) - 1]
+    cell = np.floor(th * np.float32(2.0 ** (b - 2))).astype(int)
+    assert np.all(np.diff(cell) >= 1) and cell[0] >= 0
+    assert cell[-1] < {4: 16, 5: 32, 6: 64, 7: 136, 8: 288}[b]
+
+
 # ------------------------------------------------ sensitivity refinements
 def test_cap_weights_matches_oracle():
     from oracle import sensitivity as osens

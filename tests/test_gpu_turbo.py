@@ -110,6 +110,55 @@ def test_turbo_quantize_narrow_widths(dtype):
     _check(dtype, kvc, ks, vs, Rf, bits, 32, 2, 4)
 
 
+def _token_of_norm2(S, dtype, rng):
+    """A sparse token (16-bit patterns [128]) whose squares sum to S up to
+    the remainder of the smallest value: the largest 16-bit value whose
+    square still fits, again and again."""
+    out = np.zeros(128, np.uint16)
+    rest = S
+    for c in rng.permutation(128):
+        if rest < 2.0 ** -46:
+            break
+        v16 = int(workloads.bits16_from_f32(np.array([math.sqrt(rest)], np.float32), dtype)[0])
+        v = float(workloads.u16_to_f32(np.array([v16], np.uint16), dtype)[0])
+        if v * v > rest:
+            v16 -= 1
+            v = float(workloads.u16_to_f32(np.array([v16], np.uint16), dtype)[0])
+        rest -= v * v
+        out[c] = v16 | (0x8000 if rng.random() < 0.5 else 0)
+    return out
+
+
+@pytest.mark.parametrize("dtype", [workloads.BF16, workloads.F16])
+def test_turbo_norms_at_fp16_midpoints(dtype):
+    """Norms are exact also where the sum of squares lies at, or a few
+    2^-24 beside, the square of a midpoint of two fp16 values; coordinates
+    that are exactly zero (sparse tokens, a signed permutation as rotation)
+    and zero tokens take the code below the middle threshold."""
+    torch = _torch()
+    rng = np.random.default_rng(5)
+    H, T = 4, 64
+    bits = np.array([[[1, 2], [3, 4], [5, 6], [7, 8]]])
+    r16, _ = _rotations(1, H)
+    for h in (0, 1):
+        perm = np.zeros((128, 128), np.float32)
+        perm[np.arange(128), rng.permutation(128)] = rng.choice([-1.0, 1.0], 128)
+        r16[0, h] = workloads.bits16_from_f32(perm, workloads.BF16)
+    rf = workloads.u16_to_f32(r16, workloads.BF16).astype(np.float64)
+    off = [0.0] + [s * 2.0 ** -e for e in (26, 24, 22, 21, 20, 19, 18, 17) for s in (-1, 1)]
+    kv = np.zeros((2, H, T, 128), np.uint16)
+    for i in range(2 * H * T):
+        if i % 16 == 7:
+            continue                           # a zero token
+        mid = (1.0 + (rng.integers(1024) + 0.5) / 1024) * 2.0 ** rng.integers(-3, 4)
+        kv.reshape(-1, 128)[i] = _token_of_norm2(mid * mid * (1 + off[i % len(off)]), dtype, rng)
+    kvc = rq.KVCache(rq.RQ_TURBO, dtype, 1, 1, H, H, T, 0, bits,
+                     rotation=gh.dev(r16, workloads.BF16))
+    kvc.append(0, gh.dev(kv[0][None], dtype), gh.dev(kv[1][None], dtype))
+    torch.cuda.synchronize()
+    _check(dtype, kvc, [kv[0]], [kv[1]], rf[0], bits, 0, 1, H)
+
+
 def test_turbo_quantize_wide_widths_chunked():
     bits = np.array([[[5, 6], [7, 8]]])
     kvc, ks, vs, Rf = _build(workloads.BF16, 2, 230, 40, bits, 1,
