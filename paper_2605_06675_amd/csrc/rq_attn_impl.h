@@ -550,16 +550,20 @@ typedef uint16_t us2 __attribute__((ext_vector_type(2)));
 
 // Largest of the lane's value-side scales as an fp16 pair (both halves are
 // candidates; the scales are >= 0, so their bit patterns order like them).
+// (The dwords are taken out of the vectors first: a bit_cast of a vector's
+// element reads the vector's first dword whichever element is named.)
 template <int FAM, int NA>
 __device__ __forceinline__ us2 vscale_max(const VScales<FAM, NA>& v) {
   constexpr int n = FAM == RQ_KIVI ? NA : 1;
-  us2 m = __builtin_bit_cast(us2, v.s[0].x);
+  us2 m = {0, 0};
 #pragma unroll
   for (int a = 0; a < n; ++a) {
-    if (a > 0) m = __builtin_elementwise_max(m, __builtin_bit_cast(us2, v.s[a].x));
-    m = __builtin_elementwise_max(m, __builtin_bit_cast(us2, v.s[a].y));
-    m = __builtin_elementwise_max(m, __builtin_bit_cast(us2, v.s[a].z));
-    m = __builtin_elementwise_max(m, __builtin_bit_cast(us2, v.s[a].w));
+    const uint32_t w[4] = {v.s[a].x, v.s[a].y, v.s[a].z, v.s[a].w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const us2 x = __builtin_bit_cast(us2, w[i]);
+      m = a == 0 && i == 0 ? x : __builtin_elementwise_max(m, x);
+    }
   }
   return m;
 }

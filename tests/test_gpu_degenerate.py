@@ -121,3 +121,40 @@ def test_large_values_and_queries_turbo(q_mult):
                         rotation=gh.dev(r16, workloads.BF16))
     units = gt._check(dtype, kvc, ks, vs, rf[0], bits, R, BATCH, H)
     gt._attention(kvc, units, dtype, BATCH, H, G, q_mult=q_mult)
+
+
+@pytest.mark.parametrize("family,bits", [(workloads.KIVI, [2, 4]), (workloads.RTN, [2, 3]),
+                                         (workloads.KIVI_RTN, [2, 2])],
+                         ids=["kivi", "rtn", "kivi_rtn"])
+@pytest.mark.parametrize("phase", range(4))
+def test_large_value_scales_at_some_tokens(family, bits, phase):
+    # value scales beyond 4094 at every fourth token only: a lane of the
+    # attention kernel holds four token pairs, and whichever of them carries
+    # the large scale, the value exponent has to follow (probabilities above
+    # 1 against a lagging maximum times such a scale leave fp16's range)
+    import torch
+    B, Hk, Tl = 8, 8, 4096
+    rng = np.random.default_rng(31 + phase)
+    base = rng.standard_normal((Tl, 128))
+    base[np.arange(Tl) % 4 == phase] *= 12000.0
+    v16 = workloads.bits16_from_f32(np.clip(base, -60000, 60000), workloads.F16)
+    k16 = workloads.bits16_from_f32(rng.standard_normal((Hk, Tl, 128)), workloads.F16)
+    K = gh.dev(k16, workloads.F16)[None].expand(B, Hk, Tl, 128).contiguous()
+    V = gh.dev(v16, workloads.F16)[None, None].expand(B, Hk, Tl, 128).contiguous()
+    table = np.array([[bits] * Hk])
+    kvc = rq.KVCache(family, workloads.F16, 1, B, Hk, Hk * G, Tl, 0, table)
+    kvc.append(0, K, V)
+    q16 = workloads.bits16_from_f32(2.0 * rng.standard_normal((B, Hk * G, 128)), workloads.F16)
+    out = kvc.attention(0, gh.dev(q16, workloads.F16))
+    torch.cuda.synchronize()
+    out = out.cpu().numpy()
+    assert np.all(np.isfinite(out))
+    from oracle import attention as oatt
+    for b, h in ((0, 0), (B - 1, Hk - 1)):
+        u = ocache.Unit(family, workloads.u16_to_f32(k16[h], workloads.F16),
+                        workloads.u16_to_f32(v16, workloads.F16), *bits, 0)
+        q = workloads.u16_to_f32(q16[b, h * G:(h + 1) * G], workloads.F16)
+        v_hat = u.values()
+        want = oatt.decode_attention(q, u.keys(), v_hat)
+        err = np.max(np.abs(out[b, h * G:(h + 1) * G] - want))
+        assert err < gp.attention_tol(v_hat), (b, h, err)
