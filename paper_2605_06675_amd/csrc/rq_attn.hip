@@ -21,12 +21,10 @@ size_t attention_area_bytes(int G, int wave_bytes, int family) {
   const size_t merge = (size_t)kWaves * G * (2 + kD) * sizeof(float);
   const size_t rings = (size_t)kWaves * wave_bytes;
   // the merging workgroup's scratch (and the rotation for TurboQuant) and
-  // the window staging with its scaled query rows reuse it
+  // the window's probabilities (2 KiB of each wave's ring) reuse it
   const size_t mscratch = (size_t)G * kD * sizeof(float) +
                           (family == RQ_TURBO ? (size_t)kD * kD * sizeof(uint16_t) : 0);
-  const size_t window = kResLds + (size_t)16 * kD * sizeof(float);
   size_t m = merge > rings ? merge : rings;
-  m = m > window ? m : window;
   m = m > mscratch ? m : mscratch;
   return (m + 15) / 16 * 16;
 }

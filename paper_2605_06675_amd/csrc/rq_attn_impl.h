@@ -174,6 +174,24 @@ __device__ __forceinline__ float xor_shfl(float v, int mask) {
   return __shfl_xor(v, mask, kWave);
 }
 
+// Butterfly of two registers across lane rows r and r ^ 1 (FAR: r ^ 2): the
+// lower row gets x + y, the upper x - y (x the lower row's value).
+template <bool FAR>
+__device__ __forceinline__ void row_butterfly(float& a, float& b) {
+  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+  const auto t = FAR ? __builtin_amdgcn_permlane32_swap(ua, ub, false, false)
+                     : __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
+  // t[0]: the lower rows' a, then b; t[1]: the upper rows' a, then b
+  const uint32_t t0 = t[0], t1 = t[1];
+  const float lo = __uint_as_float(t0), hi = __uint_as_float(t1);
+  const uint32_t s = __float_as_uint(lo + hi), d = __float_as_uint(lo - hi);
+  const auto u = FAR ? __builtin_amdgcn_permlane32_swap(s, d, false, false)
+                     : __builtin_amdgcn_permlane16_swap(s, d, false, false);
+  const uint32_t u0 = u[0], u1 = u[1];
+  a = __uint_as_float(u0);
+  b = __uint_as_float(u1);
+}
+
 // max of three floats (v_maximum3_f32; the operands are never NaN, and
 // fmaxf would add canonicalising moves)
 __device__ __forceinline__ float max3(float a, float b, float c) {
@@ -199,16 +217,6 @@ __device__ __forceinline__ void scale_inplace(f4& v, int i, float s) {
 // lower planes of a code, whose bits are still zero in c)
 __device__ __forceinline__ uint32_t insert(uint32_t x, uint32_t mask, uint32_t c) {
   return (x & mask) | (c & ~mask);
-}
-
-// Stores and loads of the partial results, coherent across the GPU's L2
-// caches (agent scope), so that the workgroup that merges a unit's partials
-// sees the other workgroups' results without a cache flush.
-__device__ __forceinline__ void st_agent(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_agent(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ uint32_t pk_mul(uint32_t a, uint32_t b) {
@@ -1027,16 +1035,6 @@ __device__ __forceinline__ void dispatch(int bk, int bv, const Geo& g, int depth
 #undef RQ_CASE
 }
 
-// The 16-bit query rows of this kv-head as 16-byte pieces (thread tid holds
-// piece tid: row tid / 16, channels 8 (tid % 16) ..), zero beyond G rows.
-__device__ __forceinline__ u4 query_piece(const AttnLaunch& a, int b, int h) {
-  const int tid = threadIdx.x;
-  u4 v = {0u, 0u, 0u, 0u};
-  if (tid < a.G * 16)
-    v = reinterpret_cast<const u4*>(a.q + ((size_t)b * a.H * a.G + (size_t)h * a.G) * kD)[tid];
-  return v;
-}
-
 // Copy the 16-bit query rows of this kv-head (G x 256 bytes) into qraw with
 // buffer_load_dwordx4 .. lds: wave w moves bytes [1024 w, 1024 w + 1024).
 // Returns the number of copy instructions this wave issued (0 or 1).
@@ -1051,40 +1049,6 @@ __device__ __forceinline__ int issue_query(const AttnLaunch& a, int b, int h, in
         src, (lds_void*)(reinterpret_cast<uint8_t*>(qraw) + 1024 * wave), 16,
         1024 * wave + 16 * lane, 0, 0, 0);
   return 1;
-}
-
-// Scaled query rows into qs (rows >= G zero), rotated for QuaRot.  Whole
-// workgroup; piece from query_piece.
-__device__ __forceinline__ void store_queries(const AttnLaunch& a, u4 piece, bool rotate,
-                                              float (*qs)[kD]) {
-  const int tid = threadIdx.x;
-  float f = a.qscale;
-  if (rotate) f *= kInvSqrtD;
-  const float fs = rotate ? 1.0f : f;
-  {
-    const int j = tid >> 4, c = 8 * (tid & 15);
-    const uint32_t w[4] = {piece.x, piece.y, piece.z, piece.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      qs[j][c + 2 * e] = widen(w[e] & 0xffffu, a.is_bf16) * fs;
-      qs[j][c + 2 * e + 1] = widen(w[e] >> 16, a.is_bf16) * fs;
-    }
-  }
-  __syncthreads();
-  if (rotate) {
-    for (int hh = 1; hh < kD; hh *= 2) {
-      for (int e = tid; e < a.G * (kD / 2); e += kThreads) {
-        const int j = e / (kD / 2), i = e % (kD / 2);
-        const int base = (i / hh) * 2 * hh + (i % hh);
-        const float x = qs[j][base], y = qs[j][base + hh];
-        qs[j][base] = x + y;
-        qs[j][base + hh] = x - y;
-      }
-      __syncthreads();
-    }
-    for (int e = tid; e < a.G * kD; e += kThreads) qs[e / kD][e % kD] *= f;
-    __syncthreads();
-  }
 }
 
 // TurboQuant: qs[j] = R q_j / sqrt(128) for the G query rows, on the
@@ -1163,144 +1127,208 @@ __device__ __forceinline__ void rotate_queries(const AttnLaunch& a, const TurboP
   __syncthreads();
 }
 
-// Partial of (unit, slot): float [G][2 + 128] = (max, sum, acc[128]).
-// Slots of a unit: 0 .. nw-1 streaming, nw .. nw+n_rw-1 the window,
-// then the group partials of the two-level merge.
-__device__ __forceinline__ float* part_ptr(const AttnLaunch& a, size_t unit, int slot) {
-  return a.part + (unit * a.pstride + slot) * (size_t)a.G * (2 + kD);
+// Partial results.  Slot of a unit: float acc[G][128], then (max, sum)[G].
+// Slots of a unit: 0 .. nw-1 streaming, nw .. nw+n_rw-1 the window, then the
+// group partials of the two-level merge.  Stored and loaded through a buffer
+// resource of the unit's slots, 16 bytes an instruction, with the sc1 bit:
+// agent scope, coherent across the GPU's L2 caches, so that the workgroup
+// that merges a unit's partials sees the other workgroups' results without a
+// cache flush.  (As single-dword atomics of the same scope the loads of a
+// merge of 16 slots at G = 8 took 8.3 us of the long-context launch's 49.)
+// A load at kNoSlot, beyond the resource, returns zeros: a slot of sum 0.
+constexpr int kAgentScope = 16;   // cache policy bit sc1
+constexpr uint32_t kNoSlot = 0x7fffff00u;
+
+__device__ __forceinline__ uint32_t part_slot(const AttnLaunch& a, int slot) {
+  return (uint32_t)slot * (uint32_t)a.G * ((2 + kD) * sizeof(float));
+}
+__device__ __forceinline__ uint32_t part_acc(uint32_t slot_off, int row, int c) {
+  return slot_off + (uint32_t)(row * kD + c) * sizeof(float);
+}
+__device__ __forceinline__ uint32_t part_ml(const AttnLaunch& a, uint32_t slot_off, int row) {
+  return slot_off + (uint32_t)(a.G * kD + 2 * row) * sizeof(float);
+}
+// (made anew where it is used: kept over the block loop it would cost the
+// widest variants registers they spill)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t part_of(const AttnLaunch& a, size_t unit) {
+  uint32_t u = (uint32_t)unit;
+  asm volatile("" : "+v"(u));
+  u = __builtin_amdgcn_readfirstlane(u);
+  const uint32_t n = part_slot(a, a.pstride);
+  return buffer_of(reinterpret_cast<const uint8_t*>(a.part) + (size_t)u * n, n);
 }
 
-// Residual-window staging: 64 tokens of K and of V per chunk, rows padded
-// to 272 bytes so that lanes reading different rows spread over the banks.
-constexpr int kResTok = 64;
-constexpr int kResRow = 136;   // uint16 per padded row
-constexpr size_t kResLds = (size_t)2 * kResTok * kResRow * sizeof(uint16_t);
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+template <int E>
+__device__ __forceinline__ void st_part(__amdgpu_buffer_rsrc_t p, uint32_t off, const float* v) {
+  if constexpr (E == 1)
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), p, off, 0, kAgentScope);
+  else if constexpr (E == 2)
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, ((f2){v[0], v[1]})), p, off, 0,
+                                          kAgentScope);
+  else
+#pragma unroll
+    for (int k = 0; k < E; k += 4)
+      __builtin_amdgcn_raw_buffer_store_b128(
+          __builtin_bit_cast(u4, ((f4){v[k], v[k + 1], v[k + 2], v[k + 3]})), p, off + 4 * k, 0,
+          kAgentScope);
+}
+template <int E>
+__device__ __forceinline__ void ld_part(__amdgpu_buffer_rsrc_t p, uint32_t off, float* v) {
+  if constexpr (E == 1) {
+    v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(p, off, 0, kAgentScope));
+  } else if constexpr (E == 2) {
+    const f2 x = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(p, off, 0, kAgentScope));
+    v[0] = x.x;
+    v[1] = x.y;
+  } else {
+#pragma unroll
+    for (int k = 0; k < E; k += 4) {
+      const f4 x = __builtin_bit_cast(
+          f4, __builtin_amdgcn_raw_buffer_load_b128(p, off + 4 * k, 0, kAgentScope));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[k + e] = x[e];
+    }
+  }
+}
 
-// Tokens t_lo .. t_hi-1 of the 16-bit residual window of one unit, original
-// domain.  They are read in chunks of 64 tokens staged in LDS; the loads of the next chunk (and of
-// the queries, before the first) are in flight while a chunk is computed.
-// Wave w takes query rows w, w+4, ...; lane = token for the scores, lane =
-// channel pair for PV.  stage: LDS for one chunk (kResLds bytes), qs: LDS
-// for the query rows.
+// Tokens t_lo .. t_hi-1 (at most 32) of the 16-bit residual window of one
+// unit, original domain, to partial `slot`.  One pass from registers: all
+// rows are loaded at once; Q K^T on the matrix cores from the 16-bit rows as
+// they are (exact products, fp32 sums), each wave computing all scores;
+// P V in fp32, wave w taking channels 32 w .. 32 w + 31, with the
+// probabilities passed between lanes through plds, 2 KiB of the wave's own
+// LDS.  The token this call appends is read from the new input and written
+// to its window slot here.  What bounds it is one latency of memory: 32
+// tokens took 7.5 us (G = 4) to 11.5 us (G = 8) of the launch's first
+// workgroups while they were staged in LDS and every query went over the
+// tokens by itself.
 template <bool BF16>
-__device__ __forceinline__ void residual_slot_t(const AttnLaunch& a, int b, int h,
-                                                float (*qs)[kD], uint16_t* stage,
-                                                float* dst, int t_lo, int t_hi) {
+__device__ __forceinline__ void window_chunk_t(const AttnLaunch& a, int b, int h,
+                                               __amdgpu_buffer_rsrc_t part, int slot, int t_lo,
+                                               int t_hi, float* plds) {
+  static_assert(kResChunk == 32, "two 16-token tiles");
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
-  const int cap = a.R + kChunk;
-  const uint16_t* kb = a.resid + (((size_t)b * a.H + h) * 2 + 0) * cap * kD;
-  const uint16_t* vb = a.resid + (((size_t)b * a.H + h) * 2 + 1) * cap * kD;
-  // a token appended by this call is read from the new input (its window
-  // slot is written below, by the one workgroup whose range holds it)
-  const size_t unit_row = ((size_t)b * a.H + h) * kD;
-  const uint16_t* kn = a.t_new >= 0 ? a.k_new + unit_row : kb;
-  const uint16_t* vn = a.t_new >= 0 ? a.v_new + unit_row : vb;
-  uint16_t* ks = stage;
-  uint16_t* vs = stage + kResTok * kResRow;
-  // a chunk is 64 tokens x 16 pieces of 16 bytes: four pieces per thread
-  u4 kr[4], vr[4];
-  auto load_chunk = [&](int t0) {
-    const int n = (t_hi - t0) < kResTok ? (t_hi - t0) : kResTok;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + i * kThreads, t = e >> 4, piece = e & 15;
-      if (t < n) {
-        const bool fresh = t0 + t == a.t_new;
-        const size_t row = fresh ? (size_t)piece * 8 : (size_t)((t0 + t) % cap) * kD + piece * 8;
-        kr[i] = *reinterpret_cast<const u4*>((fresh ? kn : kb) + row);
-        vr[i] = *reinterpret_cast<const u4*>((fresh ? vn : vb) + row);
-      }
-    }
+  const int col = lane & 15, g = lane >> 4;
+  const int cap = a.R + kChunk, n = t_hi - t_lo;
+  const size_t unit = (size_t)b * a.H + h;
+  const RQ_GLOBAL uint16_t* kb = gptr(a.resid) + (unit * 2 + 0) * cap * kD;
+  const RQ_GLOBAL uint16_t* vb = gptr(a.resid) + (unit * 2 + 1) * cap * kD;
+  const RQ_GLOBAL uint16_t* kn = a.t_new >= 0 ? gptr(a.k_new) + unit * kD : kb;
+  const RQ_GLOBAL uint16_t* vn = a.t_new >= 0 ? gptr(a.v_new) + unit * kD : vb;
+  const int i_new = a.t_new - t_lo;        // index of the appended token, if in 0 .. n-1
+  const int s_lo = t_lo % cap;
+  // window row of token index i (past the last token: the last one's)
+  auto row = [&](const RQ_GLOBAL uint16_t* base, const RQ_GLOBAL uint16_t* fresh, int i) {
+    i = i < n ? i : n - 1;
+    int s = s_lo + i;
+    s = s < cap ? s : s - cap;
+    return i == i_new ? fresh : base + (size_t)s * kD;
   };
-  const u4 qpiece = query_piece(a, b, h);
-  if (t_lo < t_hi) load_chunk(t_lo);
-  store_queries(a, qpiece, false, qs);
-  float m_run[4], l_run[4], ac0[4], ac1[4];
+  u4 kx[2][4], qx[4];
+  uint32_t vx[8];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    m_run[q] = -INFINITY;
-    l_run[q] = 0.0f;
-    ac0[q] = 0.0f;
-    ac1[q] = 0.0f;
+  for (int tt = 0; tt < 2; ++tt) {
+    const RQ_GLOBAL u4* r = (const RQ_GLOBAL u4*)row(kb, kn, 16 * tt + col);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) kx[tt][ks] = r[4 * ks + g];
   }
-  for (int t0 = t_lo; t0 < t_hi; t0 += kResTok) {
-    const int n = (t_hi - t0) < kResTok ? (t_hi - t0) : kResTok;
+  {
+    const RQ_GLOBAL u4* r = (const RQ_GLOBAL u4*)(gptr(a.q) + (unit * a.G + (col < a.G ? col : 0)) * kD);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) qx[ks] = r[4 * ks + g];
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    vx[k] = ((const RQ_GLOBAL uint32_t*)row(vb, vn, 8 * g + k))[16 * wave + col];
+  // scores: lane = query col, tokens 16 tt + 4g + i
+  float p[2][4], m = -INFINITY, l = 0.0f;
+#pragma unroll
+  for (int tt = 0; tt < 2; ++tt) {
+    f4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      if constexpr (BF16)
+        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(abf8, kx[tt][ks]),
+                                                    __builtin_bit_cast(abf8, qx[ks]), d, 0, 0, 0);
+      else
+        d = mfma(u4_h8(kx[tt][ks]), u4_h8(qx[ks]), d);
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int e = tid + i * kThreads, t = e >> 4, piece = e & 15;
-      if (t < n) {
-        *reinterpret_cast<u4*>(ks + t * kResRow + piece * 8) = kr[i];
-        *reinterpret_cast<u4*>(vs + t * kResRow + piece * 8) = vr[i];
-        if (t0 + t == a.t_new) {
-          uint16_t* w = a.resid_w + (size_t)(a.t_new % cap) * kD + piece * 8;
-          *reinterpret_cast<u4*>(w + (((size_t)b * a.H + h) * 2 + 0) * cap * kD) = kr[i];
-          *reinterpret_cast<u4*>(w + (((size_t)b * a.H + h) * 2 + 1) * cap * kD) = vr[i];
-        }
-      }
+      p[tt][i] = 16 * tt + 4 * g + i < n ? d[i] * a.qscale : -INFINITY;
+      m = __builtin_fmaxf(m, p[tt][i]);
     }
-    __syncthreads();
-    if (t0 + kResTok < t_hi) load_chunk(t0 + kResTok);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = wave + kWaves * q;
-      if (j >= a.G) break;
-      float s = -INFINITY;
-      if (lane < n) {
-        s = 0.0f;
-        const u4* krow = reinterpret_cast<const u4*>(ks + lane * kResRow);
-#pragma unroll 4
-        for (int c8 = 0; c8 < kD / 8; ++c8) {
-          const u4 w = krow[c8];
-          const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            s = __builtin_fmaf(qs[j][8 * c8 + 2 * e], widen_t<BF16>(ww[e] & 0xffffu), s);
-            s = __builtin_fmaf(qs[j][8 * c8 + 2 * e + 1], widen_t<BF16>(ww[e] >> 16), s);
-          }
-        }
-      }
-      float mx = s;
-      for (int d = 32; d >= 1; d >>= 1) mx = __builtin_fmaxf(mx, xor_shfl(mx, d));
-      const float mn = __builtin_fmaxf(m_run[q], mx);
-      const float al = __builtin_amdgcn_exp2f(m_run[q] - mn);
-      const float p = lane < n ? __builtin_amdgcn_exp2f(s - mn) : 0.0f;
-      float sum = p;
-      for (int d = 32; d >= 1; d >>= 1) sum += xor_shfl(sum, d);
-      l_run[q] = l_run[q] * al + sum;
-      m_run[q] = mn;
-      float c0 = ac0[q] * al, c1 = ac1[q] * al;
-#pragma unroll 8
-      for (int i = 0; i < n; ++i) {
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(vs + i * kResRow + 2 * lane);
-        const float pi = __builtin_bit_cast(
-            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, p), i));
-        c0 = __builtin_fmaf(pi, widen_t<BF16>(w & 0xffffu), c0);
-        c1 = __builtin_fmaf(pi, widen_t<BF16>(w >> 16), c1);
-      }
-      ac0[q] = c0;
-      ac1[q] = c1;
-    }
-    __syncthreads();
   }
+  m = __builtin_fmaxf(m, xor_shfl(m, 16));
+  m = __builtin_fmaxf(m, xor_shfl(m, 32));
+  const int gq = (a.G + 3) & ~3;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int j = wave + kWaves * q;
-    if (j >= a.G) break;
-    float* d = dst + (size_t)j * (2 + kD);
-    if (lane == 0) {
-      st_agent(d, m_run[q]);
-      st_agent(d + 1, l_run[q]);
+  for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float e = __builtin_amdgcn_exp2f(p[tt][i] - m);
+      l += e;
+      if (col < gq) plds[(16 * tt + 4 * g + i) * gq + col] = e;
     }
-    st_agent(d + 2 + 2 * lane, ac0[q]);
-    st_agent(d + 2 + 2 * lane + 1, ac1[q]);
+  l += xor_shfl(l, 16);
+  l += xor_shfl(l, 32);
+  __builtin_amdgcn_wave_barrier();
+  const uint32_t off = part_slot(a, slot);
+  if (wave == 0 && lane < a.G) {
+    const float ml[2] = {m, l};
+    st_part<2>(part, part_ml(a, off, lane), ml);
+  }
+  // P V: channels 32 wave + 2 col, + 1 over tokens 8g .. 8g+7, four queries
+  // at a time; then over the four lane rows, row g keeping query 4 jq + g
+  for (int jq = 0; 4 * jq < a.G; ++jq) {
+    float o[4][2] = {};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const f4 pk = *reinterpret_cast<const f4*>(plds + (8 * g + k) * gq + 4 * jq);
+      const float v0 = widen_t<BF16>(vx[k] & 0xffffu), v1 = widen_t<BF16>(vx[k] >> 16);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        o[j][0] = __builtin_fmaf(pk[j], v0, o[j][0]);
+        o[j][1] = __builtin_fmaf(pk[j], v1, o[j][1]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        o[j][e] += xor_shfl(o[j][e], 16);
+        o[j][e] += xor_shfl(o[j][e], 32);
+      }
+    const int j = 4 * jq + g;
+    float w[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      w[e] = g < 2 ? (g == 0 ? o[0][e] : o[1][e]) : (g == 2 ? o[2][e] : o[3][e]);
+    if (j < a.G) st_part<2>(part, part_acc(off, j, 32 * wave + 2 * col), w);
+  }
+  if (i_new >= 0 && i_new < n) {
+    const size_t dst = (size_t)(a.t_new % cap) * kD;
+    if (wave == 0 && col == (i_new & 15)) {
+      RQ_GLOBAL u4* w = (RQ_GLOBAL u4*)(gptr(a.resid_w) + (unit * 2 + 0) * cap * kD + dst);
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) w[4 * ks + g] = i_new < 16 ? kx[0][ks] : kx[1][ks];
+    }
+    if (g == i_new >> 3) {
+      RQ_GLOBAL uint32_t* w = (RQ_GLOBAL uint32_t*)(gptr(a.resid_w) + (unit * 2 + 1) * cap * kD + dst);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k == (i_new & 7)) w[16 * wave + col] = vx[k];
+    }
   }
 }
 
-__device__ __forceinline__ void residual_slot(const AttnLaunch& a, int b, int h,
-                                              float (*qs)[kD], uint16_t* stage,
-                                              float* dst, int t_lo, int t_hi) {
-  if (a.is_bf16) residual_slot_t<true>(a, b, h, qs, stage, dst, t_lo, t_hi);
-  else residual_slot_t<false>(a, b, h, qs, stage, dst, t_lo, t_hi);
+__device__ __forceinline__ void window_chunk(const AttnLaunch& a, int b, int h,
+                                             __amdgpu_buffer_rsrc_t part, int slot, int t_lo,
+                                             int t_hi, float* plds) {
+  if (a.is_bf16) window_chunk_t<true>(a, b, h, part, slot, t_lo, t_hi, plds);
+  else window_chunk_t<false>(a, b, h, part, slot, t_lo, t_hi, plds);
 }
 
 // Quantized blocks of workgroup slot `slot` of unit (b, h): stream, merge the
@@ -1378,7 +1406,7 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
   lo.r = lane >> 4;
   lo.col = lane & 15;
   lo.GP = a.GP;
-  lo.gsub = lo.col / a.GP;
+  lo.gsub = lo.col >> __builtin_ctz(a.GP);
   lo.tabk = lo.tabv = nullptr;
   {
     // this lane's query row j = col mod GP, channels 32 r .. 32 r + 31
@@ -1433,15 +1461,13 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
               qv[i] = x + y;
               qv[i + hh] = x - y;
             }
+// (lane rows exchanged by swaps of register pairs: two instructions
+        // a value; through ds_bpermute the 64 exchanges took half of the
+        // 4 us this set-up lasted)
 #pragma unroll
-        for (int st = 1; st <= 2; st *= 2) {
-          const bool upper = (lo.r & st) != 0;
+        for (int i = 0; i < 32; i += 2) row_butterfly<false>(qv[i], qv[i + 1]);
 #pragma unroll
-          for (int i = 0; i < 32; ++i) {
-            const float o = xor_shfl(qv[i], 16 * st);
-            qv[i] = upper ? o - qv[i] : qv[i] + o;
-          }
-        }
+        for (int i = 0; i < 32; i += 2) row_butterfly<true>(qv[i], qv[i + 1]);
 #pragma unroll
         for (int i = 0; i < 32; ++i) qv[i] *= kInvSqrtD;
       }
@@ -1520,41 +1546,43 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
   __builtin_amdgcn_s_setprio(kSetupPrio);
 
   // ---- this wave's result per query row: (m, l, out[128]) in canonical form
-  const int r = lo.r, col = lo.col, GP = a.GP;
+  const int r = lo.r, col = lo.col, GP = a.GP, lgGP = __builtin_ctz(GP);
   constexpr int GPA = 4 / NA;
-  float zt[4][4], lrow[4];
+  constexpr int VF = val_fam(FAM);
+  // KIVI: this lane's row i covers the value groups gt with gt mod GPA =
+  // (its replica) mod GPA, NA of them
+  float zt[NA][4], lrow[4], mrow[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    const int gs = (4 * r + i) >> lgGP;
+    if constexpr (VF == RQ_KIVI) {
 #pragma unroll
-    for (int gg = 0; gg < 4; ++gg) zt[gg][i] = __shfl(ws.corrZ[i], r * 16 + gg, kWave);
-    lrow[i] = __shfl(ws.corrZ[i], r * 16 + (val_fam(FAM) == RQ_KIVI ? 4 : 0), kWave);
+      for (int k = 0; k < NA; ++k)
+        zt[k][i] = __shfl(ws.corrZ[i], r * 16 + k * GPA + gs % GPA, kWave);
+    }
+    lrow[i] = __shfl(ws.corrZ[i], r * 16 + (VF == RQ_KIVI ? 4 : 0), kWave);
+    mrow[i] = __shfl(ws.m_run, (4 * r + i) & (GP - 1), kWave);
   }
-  float mrow[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) mrow[i] = __shfl(ws.m_run, (4 * r + i) & (GP - 1), kWave);
   // scale of the value sums: 2^(24+Ev) for codes as subnormals (QuaRot and
   // RTN: 2^Ev times 2^24 acc minus the offset 2^(b-1) corrO), 2^Ev / sqrt(128)
   // for TurboQuant
-  constexpr int VF = val_fam(FAM);
   const float cv = VF == RQ_TURBO ? __builtin_ldexpf(kInvSqrtD, ws.ev)
                                   : __builtin_ldexpf(1.0f, VF == RQ_QUAROT ? ws.ev : 24 + ws.ev);
   const float voff = (float)(1 << (bv - 1));
   __syncthreads();   // every wave is done with its slot
-  float* mw = merge + (size_t)wave * G * (2 + kD);
+  // per wave: float acc[G][128]; then (max, sum)[wave][G]
+  float* mw = merge + (size_t)wave * G * kD;
+  f2* mlw = reinterpret_cast<f2*>(merge + (size_t)kWaves * G * kD);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = 4 * r + i, jj = row & (GP - 1), gs = row / GP;
+    const int row = 4 * r + i, jj = row & (GP - 1), gs = row >> lgGP;
     if (jj < G) {
       if (VF == RQ_KIVI) {
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) {
           const int gt = nt / 2;
           if (gs == gt % GPA)
-            mw[jj * (2 + kD) + 2 + 16 * nt + col] = __builtin_fmaf(ws.acc[nt][i], cv, zt[gt][i]);
-        }
-        if (gs == 0 && col == 0) {
-          mw[jj * (2 + kD)] = mrow[i];
-          mw[jj * (2 + kD) + 1] = lrow[i];
+            mw[jj * kD + 16 * nt + col] = __builtin_fmaf(ws.acc[nt][i], cv, zt[gt / GPA][i]);
         }
       } else if (gs == 0) {
 #pragma unroll
@@ -1564,118 +1592,124 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
             v = __builtin_fmaf(ws.acc[nt][i], 16777216.0f, -voff * ws.corrO[i]) * cv;
           else
             v = ws.acc[nt][i] * cv;
-          mw[jj * (2 + kD) + 2 + 16 * nt + col] = v;
-        }
-        if (col == 0) {
-          mw[jj * (2 + kD)] = mrow[i];
-          mw[jj * (2 + kD) + 1] = lrow[i];
+          mw[jj * kD + 16 * nt + col] = v;
         }
       }
+      if (gs == 0 && col == 0) mlw[wave * G + jj] = (f2){mrow[i], lrow[i]};
     }
   }
   __syncthreads();
-  float* dst = part_ptr(a, unit, slot);
-  for (int e = tid; e < G * kD; e += kThreads) {
-    const int j = e / kD, cc = e % kD;
+  // the four waves' results, four channels a thread, to the slot's partial
+  const __amdgpu_buffer_rsrc_t part = part_of(a, unit);
+  const uint32_t off = part_slot(a, slot);
+  for (int e = tid; e < G * (kD / 4); e += kThreads) {
+    const int j = e / (kD / 4), c = 4 * (e % (kD / 4));
+    f2 ml[kWaves];
     float M = -INFINITY;
-    for (int w = 0; w < kWaves; ++w) M = __builtin_fmaxf(M, merge[(w * G + j) * (2 + kD)]);
-    float acc = 0.0f, l = 0.0f;
+#pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const float* src = merge + (size_t)(w * G + j) * (2 + kD);
-      const float f = (src[0] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(src[0] - M);
-      acc = __builtin_fmaf(f, src[2 + cc], acc);
-      l = __builtin_fmaf(f, src[1], l);
+      ml[w] = mlw[w * G + j];
+      M = __builtin_fmaxf(M, ml[w].x);
     }
-    st_agent(dst + j * (2 + kD) + 2 + cc, acc);
-    if (cc == 0) {
-      st_agent(dst + j * (2 + kD), M);
-      st_agent(dst + j * (2 + kD) + 1, l);
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+    float l = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const f4 v = *reinterpret_cast<const f4*>(merge + (size_t)(w * G + j) * kD + c);
+      const float f = ml[w].x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ml[w].x - M);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[k] = __builtin_fmaf(f, v[k], acc[k]);
+      l = __builtin_fmaf(f, ml[w].y, l);
     }
+    const float o[4] = {acc[0], acc[1], acc[2], acc[3]}, o2[2] = {M, l};
+    st_part<4>(part, part_acc(off, j, c), o);
+    if (c == 0) st_part<2>(part, part_ml(a, off, j), o2);
   }
 }
 
 // Merge partials of one (batch, kv-head) unit: slots first .. first+count-1
 // (quantized blocks: QuaRot and TurboQuant in the rotated domain) and the
 // nwin window slots win .. win+nwin-1 (original domain).  dst: a partial
-// slot to write the merged (max, sum, acc) to, or NULL to write the unit's
+// slot to write the merged (max, sum, acc) to, or -1 to write the unit's
 // output.  Thread t owns E consecutive elements of one query row (E = 128 Gp
-// / 256, Gp the power of two >= G), so a slot's (max, sum) is loaded once
-// per row segment; the loads of several slots are in flight together.
+// / 256, Gp the power of two >= G); up to kS slots are loaded at once, the
+// missing ones as zeros, so that a merge of up to 16 slots is one latency.
 // Whole workgroup; lds: scratch of 128 G floats, plus the rotation
 // (TurboQuant, 32 KB).
 template <int E>
-__device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit, float* lds,
-                                           int first, int count, int win, int nwin,
-                                           float* dst) {
-  constexpr int kS = E <= 2 ? 16 : (E == 4 ? 12 : 6);
+__device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit,
+                                           __amdgpu_buffer_rsrc_t part, float* lds, int first,
+                                           int count, int win, int nwin, int dst) {
+  constexpr int kS = E <= 4 ? 16 : 8;
   constexpr int TPR = kD / E;              // threads per row
   const int tid = threadIdx.x;
   const int G = a.G;
   const int j = tid / TPR, c0 = (tid % TPR) * E;
   const bool own = j < G;
   const int ns = count + nwin;
-  const float* base = part_ptr(a, unit, 0) + (size_t)j * (2 + kD);
-  const size_t stride = (size_t)G * (2 + kD);
-  // TurboQuant output: the unit's rotation (32 KB) is loaded now, in flight
-  // with the partials, and staged in LDS after them
-  constexpr int kRotLoads = kD * kD / 8 / kThreads;
-  const bool turbo_out = !dst && a.family == RQ_TURBO;
-  u4 rtmp[kRotLoads];
-  if (turbo_out) {
-    const RQ_GLOBAL u4* src = gptr(reinterpret_cast<const u4*>(
-        a.rot + (size_t)(unit % a.H) * kD * kD));
+  // TurboQuant output: the unit's rotation (32 KB) is copied to LDS behind
+  // the quantized-domain sums, in flight with the partials
+  uint16_t* Rs = reinterpret_cast<uint16_t*>(lds + G * kD);
+  if (dst < 0 && a.family == RQ_TURBO) {
+    constexpr int kRotBytes = kD * kD * 2;
+    const __amdgpu_buffer_rsrc_t rot =
+        buffer_of(a.rot + (size_t)(unit % a.H) * kD * kD, kRotBytes);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 #pragma unroll
-    for (int k = 0; k < kRotLoads; ++k) rtmp[k] = src[tid + k * kThreads];
+    for (int k = 0; k < kRotBytes / (16 * kThreads); ++k)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rot, (lds_void*)(reinterpret_cast<uint8_t*>(Rs) + 16 * kThreads * k + 16 * kWave * wave),
+          16, 16 * kThreads * k + 16 * tid, 0, 0, 0);
   }
   float M = -INFINITY, den = 0.0f, num[E], tail[E];
 #pragma unroll
   for (int k = 0; k < E; ++k) num[k] = tail[k] = 0.0f;
-  if (own) {
-    for (int s0 = 0; s0 < ns; s0 += kS) {
-      float m[kS], l[kS], v[kS][E];
+  for (int s0 = 0; s0 < ns; s0 += kS) {
+    float ml[kS][2], v[kS][E];
 #pragma unroll
-      for (int i = 0; i < kS; ++i) {
-        m[i] = -INFINITY;
-        l[i] = 0.0f;
+    for (int i = 0; i < kS; ++i) {
+      const int q = s0 + i;
+      const bool any = own && q < ns;
+      const uint32_t so = part_slot(a, q < count ? first + q : win + (q - count));
+      ld_part<2>(part, any ? part_ml(a, so, j) : kNoSlot, ml[i]);
+      ld_part<E>(part, any ? part_acc(so, j, c0) : kNoSlot, v[i]);
+    }
+    float mn = M;
 #pragma unroll
-        for (int k = 0; k < E; ++k) v[i][k] = 0.0f;
-        if (s0 + i < ns) {
-          const int slot = s0 + i < count ? first + s0 + i : win + (s0 + i - count);
-          const float* src = base + slot * stride;
-          m[i] = ld_agent(src);
-          l[i] = ld_agent(src + 1);
+    for (int i = 0; i < kS; ++i) {
+      if (!(ml[i][1] > 0.0f)) ml[i][0] = -INFINITY;
+      mn = __builtin_fmaxf(mn, ml[i][0]);
+    }
+    const float ref = mn == -INFINITY ? 0.0f : mn;
+    const float fo = __builtin_amdgcn_exp2f(M - ref);
+    M = mn;
+    den *= fo;
 #pragma unroll
-          for (int k = 0; k < E; ++k) v[i][k] = ld_agent(src + 2 + c0 + k);
-        }
-      }
+    for (int k = 0; k < E; ++k) {
+      num[k] *= fo;
+      tail[k] *= fo;
+    }
 #pragma unroll
-      for (int i = 0; i < kS; ++i) {
-        if (!(l[i] > 0.0f)) continue;
-        const float mn = __builtin_fmaxf(M, m[i]);
-        const float fo = __builtin_amdgcn_exp2f(M - mn);
-        const float fi = __builtin_amdgcn_exp2f(m[i] - mn);
-        M = mn;
-        den = __builtin_fmaf(den, fo, fi * l[i]);
-        // the window slot is in the original domain: kept apart
-        const bool w = s0 + i >= count;
+    for (int i = 0; i < kS; ++i) {
+      const float f = __builtin_amdgcn_exp2f(ml[i][0] - ref);
+      den = __builtin_fmaf(f, ml[i][1], den);
+      // the window slots are in the original domain: kept apart
+      if (s0 + i >= count) {
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-          num[k] = num[k] * fo + (w ? 0.0f : fi * v[i][k]);
-          tail[k] = tail[k] * fo + (w ? fi * v[i][k] : 0.0f);
-        }
+        for (int k = 0; k < E; ++k) tail[k] = __builtin_fmaf(f, v[i][k], tail[k]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < E; ++k) num[k] = __builtin_fmaf(f, v[i][k], num[k]);
       }
     }
   }
-  if (dst) {
+  if (dst >= 0) {
     // a group partial (no window in it)
     if (own) {
-      float* d = dst + (size_t)j * (2 + kD);
-      if (c0 == 0) {
-        st_agent(d, M);
-        st_agent(d + 1, den);
-      }
-#pragma unroll
-      for (int k = 0; k < E; ++k) st_agent(d + 2 + c0 + k, num[k]);
+      const uint32_t so = part_slot(a, dst);
+      const float o[2] = {M, den};
+      if (c0 == 0) st_part<2>(part, part_ml(a, so, j), o);
+      st_part<E>(part, part_acc(so, j, c0), num);
     }
     return;
   }
@@ -1711,9 +1745,7 @@ __device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit, flo
     return;
   }
   // TurboQuant: x = R^T y, R staged in LDS (row-major, as stored)
-  uint16_t* Rs = reinterpret_cast<uint16_t*>(lds + G * kD);
-#pragma unroll
-  for (int k = 0; k < kRotLoads; ++k) reinterpret_cast<u4*>(Rs)[tid + k * kThreads] = rtmp[k];
+  wait_vm<0>();
   __syncthreads();
   if (own) {
     float acc[E];
@@ -1730,17 +1762,17 @@ __device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit, flo
   }
 }
 
-__device__ __forceinline__ void merge_slots(const AttnLaunch& a, size_t unit, float* lds,
-                                            int first, int count, int win, int nwin,
-                                            float* dst) {
+__device__ __forceinline__ void merge_slots(const AttnLaunch& a, size_t unit,
+                                            __amdgpu_buffer_rsrc_t part, float* lds, int first,
+                                            int count, int win, int nwin, int dst) {
   if (a.GP <= 2)
-    merge_rows<1>(a, unit, lds, first, count, win, nwin, dst);
+    merge_rows<1>(a, unit, part, lds, first, count, win, nwin, dst);
   else if (a.GP <= 4)
-    merge_rows<2>(a, unit, lds, first, count, win, nwin, dst);
+    merge_rows<2>(a, unit, part, lds, first, count, win, nwin, dst);
   else if (a.GP <= 8)
-    merge_rows<4>(a, unit, lds, first, count, win, nwin, dst);
+    merge_rows<4>(a, unit, part, lds, first, count, win, nwin, dst);
   else
-    merge_rows<8>(a, unit, lds, first, count, win, nwin, dst);
+    merge_rows<8>(a, unit, part, lds, first, count, win, nwin, dst);
 }
 
 // Arrival tickets on the unit's counters (agent scope); the caller's
@@ -1789,36 +1821,39 @@ attn_kernel(AttnLaunch a) {
   // (workgroups go to the XCDs round-robin).  Block claims then balance
   // each unit over fast and slow slots alike.
   const int n_units = a.B * a.H;
-  const int slot = blockIdx.x / n_units;
-  const size_t unit = (blockIdx.x + slot) % n_units;
-  const int h = (int)(unit % a.H), b = (int)(unit / a.H);
+  // (the divisions run on the vector unit: their results back in scalars)
+  const int slot = __builtin_amdgcn_readfirstlane(blockIdx.x / n_units);
+  const size_t unit = (uint32_t)__builtin_amdgcn_readfirstlane((blockIdx.x + slot) % n_units);
+  const int b = __builtin_amdgcn_readfirstlane((int)unit / a.H), h = (int)unit - b * a.H;
   // this unit's workgroups (its kv-head's share of the grid; slots beyond
-  // it have nothing to do)
+  // have nothing to do): nw streaming blocks and, where the grid leaves CUs
+  // idle, one per window chunk
   const int nw = a.nwg[h];
-  const int nx = nw > 0 ? nw : 1;
+  const int nx = a.win_wg ? nw + a.n_rw : nw > 0 ? nw : 1;
   if (slot >= nx) return;
   // Set-up, the window, the partial write and the merges run at a raised
   // wave priority: they share SIMDs with other workgroups' block loops, and
   // a unit finishes only after its slowest set-up and its merge, so they
   // go first; the block loops run at normal priority.
   __builtin_amdgcn_s_setprio(kSetupPrio);
-  // The unit's nx workgroups: slot s first takes the 16-bit window chunks
-  // s, s + nx, .. (kResChunk tokens each, partial nw + chunk; the area is
-  // their staging), then streams its share of the quantized blocks (slots
-  // 0 .. nw-1).  The window thus costs a few workgroups some of their
-  // blocks (the claims hand those to the others) instead of holding
-  // workgroups of its own.
-  for (int c = slot; c < a.n_rw; c += nx) {
+  // The 16-bit window, kResChunk tokens a chunk, chunk c to partial nw + c.
+  // With workgroups of its own (win_wg) chunk c belongs to slot nw + c.
+  // Else slot s first takes the chunks s, s + nx, .. and then streams its
+  // share of the quantized blocks: the window then costs a few workgroups
+  // some of their blocks (the claims hand those to the others) instead of
+  // holding workgroups that blocks could use.
+  for (int c = a.win_wg ? slot - nw : slot; c >= 0 && c < a.n_rw; c += nx) {
     const int t_lo = a.nq + c * kResChunk;
     const int t_hi = t_lo + kResChunk < a.n_tokens ? t_lo + kResChunk : a.n_tokens;
-    residual_slot(a, b, h, reinterpret_cast<float (*)[kD]>(slots + kResLds),
-                  reinterpret_cast<uint16_t*>(slots), part_ptr(a, unit, nw + c), t_lo, t_hi);
-    __syncthreads();   // the staging area is reused
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    window_chunk(a, b, h, part_of(a, unit), nw + c, t_lo, t_hi,
+                 reinterpret_cast<float*>(slots + (size_t)wave * a.wave_bytes));
+    // the block stream counts this wave's memory operations from zero: the
+    // window's partial stores complete first
+    wait_vm<0>();
   }
-  // the block stream counts this wave's memory operations from zero: the
-  // window's partial stores complete first
-  if (slot < a.n_rw) wait_vm<0>();
-  if (slot < nw) stream_slot<FAM, NA, MAXB>(a, slot, nw, h, b, qs, qraw, cst, slots, merge);
+  if (slot < nw)
+    stream_slot<FAM, NA, MAXB>(a, slot, nw, h, b, qs, qraw, cst, slots, merge);
   // publish this workgroup's partials and take a ticket.  Up to
   // kAttnMergeFlat workgroups: the last to arrive merges every slot and the
   // window.  More: they report in groups of kGroup, the last of a group
@@ -1830,7 +1865,7 @@ attn_kernel(AttnLaunch a) {
   const int ng = (nw + kGroup - 1) / kGroup;
   if (nw <= kAttnMergeFlat) {
     if (take_ticket(cnt, ep) == (uint32_t)(nx - 1)) {
-      merge_slots(a, unit, merge, 0, nw, nw, a.n_rw, nullptr);
+      merge_slots(a, unit, part_of(a, unit), merge, 0, nw, nw, a.n_rw, -1);
       reset_counter(cnt, ep);
       // every claim group's line (the last arrival: nobody claims now)
       for (int g = 0; g < (ng > 1 ? ng : 1); ++g) reset_counter(cnt + a.claim_off + 16 * g, ep);
@@ -1843,14 +1878,13 @@ attn_kernel(AttnLaunch a) {
     const int gsz = nw - g * kGroup < kGroup ? nw - g * kGroup : kGroup;
     if (take_ticket(cnt + 1 + g, ep) != (uint32_t)(gsz - 1)) return;
     __syncthreads();   // the merge area is read until here
-    merge_slots(a, unit, merge, g * kGroup, gsz, 0, 0,
-                part_ptr(a, unit, nw + a.n_rw + g));
+    merge_slots(a, unit, part_of(a, unit), merge, g * kGroup, gsz, 0, 0, nw + a.n_rw + g);
     reset_counter(cnt + 1 + g, ep);
     // every wave of the group has stopped claiming
     reset_counter(cnt + a.claim_off + 16 * g, ep);
   }
   if (take_ticket(cnt, ep) != (uint32_t)(ng - 1)) return;
-  merge_slots(a, unit, merge, nw + a.n_rw, ng, nw, a.n_rw, nullptr);
+  merge_slots(a, unit, part_of(a, unit), merge, nw + a.n_rw, ng, nw, a.n_rw, -1);
   reset_counter(cnt, ep);
 }
 

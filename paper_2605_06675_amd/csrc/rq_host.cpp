@@ -159,6 +159,7 @@ struct SplitPlan {
   int nq, n_rw;
   int n_wg;                          // the largest nwg (grid slots per unit)
   int nwg[RQ_MAX_KV_HEADS];          // workgroups per unit of each kv-head
+  int win_wg;                        // the window's chunks have their own
   int pstride;                       // partial slots per unit
 };
 
@@ -221,8 +222,10 @@ int merge_groups(int n_wg) {
 // blocks per workgroup.  (Shares weighted by the cost of each kv-head's
 // widths were measured slower on MI355X: a unit's extra workgroups land in
 // the youngest residency slots, which issue last.)  The 16-bit window is
-// n_rw chunks of 32 tokens, taken by the unit's first workgroups before
-// their blocks.
+// n_rw chunks of 32 tokens.  Where the resident round has room for a
+// workgroup per chunk besides the streaming ones (short contexts, small
+// batches: a call there is one latency after another) each chunk gets one;
+// else the unit's first workgroups take the chunks before their blocks.
 SplitPlan plan_splits(const rq_cache* c, int layer, int n_tokens, int wg_per_cu = 3) {
   (void)layer;
   SplitPlan p{};
@@ -243,6 +246,11 @@ SplitPlan plan_splits(const rq_cache* c, int layer, int n_tokens, int wg_per_cu 
     const int ps = p.nwg[h] + p.n_rw + merge_groups(p.nwg[h]);
     p.pstride = ps > p.pstride ? ps : p.pstride;
   }
+  // (a unit has one workgroup at the least, so beside none streaming the
+  // chunks always fit; the two-level merge counts streaming ones only)
+  const int wide = p.n_wg + p.n_rw;
+  p.win_wg = p.n_rw > 0 && (p.n_wg == 0 || wide <= (long)budget) && wide <= rq::kAttnMergeFlat;
+  if (p.win_wg) p.n_wg = wide;
   return p;
 }
 
@@ -370,6 +378,7 @@ rq_status decode_attention(const rq_cache* c, int32_t layer, int32_t n_tokens, c
   a.n_wg = p.n_wg;
   for (int h = 0; h < c->n_kv_heads; ++h) a.nwg[h] = (uint16_t)p.nwg[h];
   a.n_rw = p.n_rw;
+  a.win_wg = p.win_wg;
   a.is_bf16 = c->dtype == RQ_BF16;
   a.family = c->family;
   a.qscale = scale * 1.4426950408889634f;

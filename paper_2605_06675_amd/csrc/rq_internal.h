@@ -89,7 +89,8 @@ struct AttnLaunch {
   const uint16_t* v_new;
   uint16_t* resid_w;      // this layer's window, writable
   int t_new;
-  float* part;            // [B][H][pstride][G][2 + 128] (max, sum, acc);
+  float* part;            // [B][H][pstride] slots of float acc[G][128],
+                          // (max, sum)[G];
                           // slots 0..n_wg-1 streaming, n_wg..n_wg+n_rw-1
                           // the residual window, then one per merge group
   uint64_t* counters;     // [B][H][cstride] arrival and claim counters:
@@ -105,7 +106,8 @@ struct AttnLaunch {
   int nq, n_tokens;
   int n_wg;               // grid slots per unit: the largest nwg[h]
   uint16_t nwg[RQ_MAX_KV_HEADS];  // workgroups streaming blocks, per kv-head
-  int n_rw;               // workgroups per unit on the 16-bit window
+  int n_rw;               // chunks of the 16-bit window (kAttnResChunk tokens)
+  int win_wg;             // 1: each chunk has a workgroup of its own
   int wave_bytes;         // LDS bytes of one wave's block ring
   int area_bytes;         // LDS bytes of the ring/merge/staging area
   int is_bf16, family;
