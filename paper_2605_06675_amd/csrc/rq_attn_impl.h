@@ -192,6 +192,13 @@ __device__ __forceinline__ void row_butterfly(float& a, float& b) {
   b = __uint_as_float(u1);
 }
 
+// v of the lane N columns before (modulo 16) in the same row of lanes
+template <int N>
+__device__ __forceinline__ float row_ror(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(
+      0, (int)__float_as_uint(v), 0x120 + N, 0xF, 0xF, true));
+}
+
 // max of three floats (v_maximum3_f32; the operands are never NaN, and
 // fmaxf would add canonicalising moves)
 __device__ __forceinline__ float max3(float a, float b, float c) {
@@ -245,13 +252,6 @@ __device__ __forceinline__ uint32_t quarter3(const uint32_t* wds, int q) {
   if (q == 2) return spread3(__builtin_amdgcn_alignbit(wds[2], wds[1], 16));
   return spread3(wds[2] >> 8);
 }
-// quarter r (per lane) of the chunk at ch, spread: one aligned funnel
-// shift of words (24r / 32, 24r / 32 + 1).  For r = 3 the second word is
-// the one after the chunk; the bits taken from it land above bit 27.
-__device__ __forceinline__ uint32_t lane_quarter3(const uint32_t* ch, int r) {
-  const int w = (24 * r) >> 5;
-  return spread3(__builtin_amdgcn_alignbit(ch[w + 1], ch[w], (24 * r) & 31));
-}
 // slot s of a spread quarter as a pair of fields at bits (P, 16+P), P =
 // 3s for s < 3 and 0 for s = 3 (a field at bit 9 would reach the exponent)
 __device__ __forceinline__ uint32_t slot3(uint32_t z, int s) {
@@ -276,31 +276,60 @@ __device__ __forceinline__ uint32_t kpair(const uint32_t* wds, int i) {
   return acc;
 }
 
-// fp16 pairs (u 2^(P-24)) of value slots i = 0..3 (codes 4r+i, 16+4r+i) of
-// one channel's chunk (its B words in LDS), P = vpos(B, i).
+// The words of one channel's chunk (ch, B words in LDS) that hold the codes
+// 4r+i and 16+4r+i (i = 0..3) of lane quarter r, read ahead of their use.
+template <int B> struct VWords {
+  static constexpr int n = B == 3 || plane_w(B, 0) == 8 ? 2 : plane_n(B);
+  uint32_t w[n];
+};
 template <int B>
-__device__ __forceinline__ void vpairs(const uint32_t* ch, int r, uint32_t out[4]) {
+__device__ __forceinline__ VWords<B> load_vwords(const uint32_t* ch, int r) {
+  VWords<B> v;
+  if constexpr (B == 3) {
+    // quarter r lies in words 24r / 32 and the next (for r = 3 the one after
+    // the chunk, of which no bit below 28 is taken)
+    const int w = (24 * r) >> 5;
+    v.w[0] = ch[w];
+    v.w[1] = ch[w + 1];
+  } else if constexpr (plane_w(B, 0) == 8) {
+    v.w[0] = ch[2 * r];
+    v.w[1] = ch[2 * r + 1];
+  } else {
+#pragma unroll
+    for (int p = 0; p < plane_n(B); ++p)
+      v.w[p] = ch[plane_off(B, p) + (4 * r) / (16 / plane_w(B, p))];
+  }
+  return v;
+}
+// bit of quarter r's first field in plane p's word
+__device__ __forceinline__ int vfield(int b, int p, int r) {
+  const int w = plane_w(b, p);
+  return ((4 * r) % (16 / w)) * w;
+}
+
+// fp16 pairs (u 2^(P-24)) of value slots i = 0..3 (codes 4r+i, 16+4r+i) of
+// one channel's chunk, P = vpos(B, i).
+template <int B>
+__device__ __forceinline__ void vpairs(const VWords<B>& v, int r, uint32_t out[4]) {
   constexpr int w0 = plane_w(B, 0);
   if constexpr (B == 3) {
-    const uint32_t z = lane_quarter3(ch, r);
+    const uint32_t z = spread3(__builtin_amdgcn_alignbit(v.w[1], v.w[0], (24 * r) & 31));
 #pragma unroll
     for (int i = 0; i < 4; ++i) out[i] = slot3(z, i);
   } else if constexpr (w0 == 8) {
-    const uint32_t x = ch[2 * r], y = ch[2 * r + 1];
-    out[0] = x & pair_mask(8);
-    out[1] = (x >> 8) & pair_mask(8);
-    out[2] = y & pair_mask(8);
-    out[3] = (y >> 8) & pair_mask(8);
+    out[0] = v.w[0] & pair_mask(8);
+    out[1] = (v.w[0] >> 8) & pair_mask(8);
+    out[2] = v.w[1] & pair_mask(8);
+    out[3] = (v.w[1] >> 8) & pair_mask(8);
   } else {
-    constexpr int per = 16 / w0;
-    const uint32_t x = ch[(4 * r) / per] >> (((4 * r) % per) * w0);
+    const uint32_t x = v.w[0] >> vfield(B, 0, r);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       out[i] = (x >> vshift(B, i)) & (pair_mask(w0) << vpos(B, i));
 #pragma unroll
     for (int p = 1; p < plane_n(B); ++p) {
-      const int w = plane_w(B, p), pp = 16 / w, off = plane_off(B, p);
-      const uint32_t y = ch[off + (4 * r) / pp] >> (((4 * r) % pp) * w);
+      const int w = plane_w(B, p), off = plane_off(B, p);
+      const uint32_t y = v.w[p] >> vfield(B, p, r);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int tgt = vpos(B, i) + off;
@@ -312,8 +341,7 @@ __device__ __forceinline__ void vpairs(const uint32_t* ch, int r, uint32_t out[4
 
 // ------------------------------------------------------------- TurboQuant
 // Codes (i, i + 16) of a chunk as integers at bits 0 and 16 (i < 16 after
-// unrolling, or, for widths other than three, a per-lane quarter base plus
-// a constant).
+// unrolling).
 template <int B>
 __device__ __forceinline__ uint32_t tq_code_pair(const uint32_t* wds, int i) {
   // three bits: the fields at bits (0, 16); the bits above them are not
@@ -394,6 +422,41 @@ __device__ __forceinline__ uint32_t tq_pair(const uint32_t* wds, int i, uint32_t
   else return tq_lds(tq_code2_pair<B>(wds, i), tab);
 }
 
+// fp16 centroid pairs of value slots i = 0..3 of one channel's chunk
+template <int B>
+__device__ __forceinline__ void tq_vpairs(const VWords<B>& v, int r, uint32_t lut, lds_h* tab,
+                                          uint32_t out[4]) {
+  if constexpr (B == 3) {
+    const uint32_t z = spread3(__builtin_amdgcn_alignbit(v.w[1], v.w[0], (24 * r) & 31));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = tq_tab<3>((z >> (3 * i)) & pair_mask(3), tab);
+  } else {
+    // the fields of slot i at bits i w (8-bit codes: 8 (i & 1) of word i / 2)
+    uint32_t x[VWords<B>::n];
+#pragma unroll
+    for (int p = 0; p < VWords<B>::n; ++p)
+      x[p] = plane_w(B, 0) == 8 ? v.w[p] : v.w[p] >> vfield(B, p, r);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      // codes (wider than four bits: codes times two) at bits 0 and 16
+      constexpr int up = B >= 5 ? 1 : 0;
+      uint32_t f = 0;
+      if constexpr (plane_w(B, 0) == 8) {
+        f = shr_signed(x[i >> 1], 8 * (i & 1) - up) & (pair_mask(8) << up);
+      } else {
+#pragma unroll
+        for (int p = 0; p < plane_n(B); ++p) {
+          const int w = plane_w(B, p), off = plane_off(B, p);
+          f |= shr_signed(x[p], i * w - off - up) & (pair_mask(w) << (off + up));
+        }
+      }
+      if constexpr (B == 1) out[i] = tq_lut1(f, lut);
+      else if constexpr (B <= 4) out[i] = tq_tab<B>(f, tab);
+      else out[i] = tq_lds(f, tab);
+    }
+  }
+}
+
 // Key-side and value-side paths of a family.  The mixed family (KIVI keys,
 // RTN values) takes the KIVI path for its keys and the per-token symmetric
 // path (the QuaRot instantiation, queries left unrotated) for its values.
@@ -415,11 +478,15 @@ struct WaveState {
 };
 
 // Static per-lane operands built once per workgroup.
+template <int NA>
 struct LaneOps {
   uint32_t qh[16];  // QK B operand: fp16 q' 2^-(kpos + e) per k-slot pair
                     // (TurboQuant: q' 2^-e), q' the query (QuaRot: H q /
                     // sqrt(128), TurboQuant: R q / sqrt(128))
-  uint32_t qz[16];  // KIVI: fp16 q' 2^-e per k-slot pair (zero-point term)
+  uint32_t qm[NA < 4 ? 16 : 1];  // KIVI, replicated columns: qh in the odd
+                    //   replicas, 0 in the even ones (see kpart)
+  uint32_t qz[4 * NA];  // KIVI: fp16 q' 2^-e of the chunks m (4 / NA) + this
+                    //   lane's replica, m < NA (zero-point term)
   uint32_t vq[4];   // QuaRot/RTN: fp16 pair 2^vpos(i) of value slot i
   f4 corrK;         // QuaRot/RTN: -2^(b-1) sum_c 2^(kpos-24) qh (start value
                     // of the score accumulators; the same in all rows)
@@ -446,8 +513,8 @@ struct SlotPtrs {
 // scores of this lane's query relative to m_ref.  A operands: tile t
 // (tokens 16t..16t+15, row = col), k-slot pairs (kb, k') of chunk r,
 // unpacked per K-step.
-template <int FAM, int BK>
-__device__ __forceinline__ void kpart(const SlotPtrs& sp, const LaneOps& lo, float m_ref,
+template <int FAM, int NA, int BK>
+__device__ __forceinline__ void kpart(const SlotPtrs& sp, const LaneOps<NA>& lo, float m_ref,
                                       f4& t0, f4& t1) {
   const int r = lo.r;
   uint32_t kw[2][BK];
@@ -460,38 +527,67 @@ __device__ __forceinline__ void kpart(const SlotPtrs& sp, const LaneOps& lo, flo
     // per-channel scales folded into the query as an exact fp16 pair
     // hi + lo = q' s 2^-(kpos+e) (hi the rounded product, lo its rounding
     // error), both against the same codes; the zero points enter through
-    // their own chain X = sum_c z_c q'_c 2^-e, the same in all rows
+    // their own sum X = sum_c z_c q'_c 2^-e.
+    // The sixteen columns hold the queries 4 / NA times over (NA < 4), and a
+    // matrix instruction takes as long as five vector ones, also from the
+    // other waves of its SIMD.  So the even replicas carry hi and the odd
+    // ones lo (q' s - 0 = hi, or q' s - hi, one fma), and the two halves of
+    // a score meet by a rotation of the columns: 8 instructions in place of
+    // 16.  X: row and replica rho of one instruction take chunk rho of
+    // the zero points and of the query, whose products are the diagonal
+    // blocks of the result; NA instructions in place of 4.
+    constexpr int RP = 4 / NA;     // replicas
     f4 X = {0.f, 0.f, 0.f, 0.f};
     S0 = X;
     S1 = X;
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      const u4 s4 = sp.km[r * 8 + kb], z4 = sp.km[r * 8 + 4 + kb];
-      const uint32_t s[4] = {s4.x, s4.y, s4.z, s4.w};
-      uint32_t hi[4], lw[4];
+    for (int m = 0; m < NA; ++m)
+      X = mfma(u4_h8(sp.km[r * 8 + 4 + m * RP + (RP > 1 ? lo.col & (RP - 1) : 0)]),
+               make_h8(lo.qz[4 * m], lo.qz[4 * m + 1], lo.qz[4 * m + 2], lo.qz[4 * m + 3]), X);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        hi[i] = pk_mul(lo.qh[4 * kb + i], s[i]);
-        lw[i] = pk_fms(lo.qh[4 * kb + i], s[i], hi[i]);
-      }
-      const h8 Bhi = make_h8(hi[0], hi[1], hi[2], hi[3]);
-      const h8 Blo = make_h8(lw[0], lw[1], lw[2], lw[3]);
-      X = mfma(u4_h8(z4), make_h8(lo.qz[4 * kb], lo.qz[4 * kb + 1], lo.qz[4 * kb + 2],
-                                  lo.qz[4 * kb + 3]), X);
+    for (int kb = 0; kb < 4; ++kb) {
+      const u4 s4 = sp.km[r * 8 + kb];
+      const uint32_t s[4] = {s4.x, s4.y, s4.z, s4.w};
       const h8 A0 = make_h8(kpair<BK>(kw[0], 4 * kb), kpair<BK>(kw[0], 4 * kb + 1),
                             kpair<BK>(kw[0], 4 * kb + 2), kpair<BK>(kw[0], 4 * kb + 3));
       const h8 A1 = make_h8(kpair<BK>(kw[1], 4 * kb), kpair<BK>(kw[1], 4 * kb + 1),
                             kpair<BK>(kw[1], 4 * kb + 2), kpair<BK>(kw[1], 4 * kb + 3));
-      S0 = mfma(A0, Bhi, S0);
-      S1 = mfma(A1, Bhi, S1);
+      uint32_t hi[4], lw[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        hi[i] = pk_mul(RP > 1 ? lo.qm[4 * kb + i] : lo.qh[4 * kb + i], s[i]);
+        lw[i] = pk_fms(lo.qh[4 * kb + i], s[i], hi[i]);
+      }
+      const h8 Blo = make_h8(lw[0], lw[1], lw[2], lw[3]);
+      if constexpr (RP == 1) {
+        const h8 Bhi = make_h8(hi[0], hi[1], hi[2], hi[3]);
+        S0 = mfma(A0, Bhi, S0);
+        S1 = mfma(A1, Bhi, S1);
+      }
       S0 = mfma(A0, Blo, S0);
       S1 = mfma(A1, Blo, S1);
     }
-    const float xx = __builtin_fmaf(X[0], lo.eK, -m_ref);
+    float x = X[0];
+    if constexpr (RP == 4) {
+      // replica rho = lo.gsub: the diagonal element, then the four replicas
+      x = (lo.gsub & 2) ? ((lo.gsub & 1) ? X[3] : X[2]) : ((lo.gsub & 1) ? X[1] : X[0]);
+      x += row_ror<4>(x);
+      x += row_ror<8>(x);
+    } else if constexpr (RP == 2) {
+      x = (lo.gsub & 1) ? X[1] : X[0];
+      x += row_ror<8>(x);
+    }
+    const float xx = __builtin_fmaf(x, lo.eK, -m_ref);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      t0[i] = __builtin_fmaf(S0[i], lo.cK, xx);
-      t1[i] = __builtin_fmaf(S1[i], lo.cK, xx);
+      float a = S0[i], b = S1[i];
+      if constexpr (RP > 1) {
+        // the other half of the score, one replica over
+        a += row_ror<16 / RP>(a);
+        b += row_ror<16 / RP>(b);
+      }
+      t0[i] = __builtin_fmaf(a, lo.cK, xx);
+      t1[i] = __builtin_fmaf(b, lo.cK, xx);
     }
   } else {
     S0 = FAM == RQ_TURBO ? (f4){0.f, 0.f, 0.f, 0.f} : lo.corrK;
@@ -542,7 +638,7 @@ struct VScales {
 };
 
 template <int FAM, int NA>
-__device__ __forceinline__ VScales<FAM, NA> load_vscales(const SlotPtrs& sp, const LaneOps& lo) {
+__device__ __forceinline__ VScales<FAM, NA> load_vscales(const SlotPtrs& sp, const LaneOps<NA>& lo) {
   VScales<FAM, NA> v;
   if constexpr (FAM == RQ_KIVI) {
     constexpr int GPA = 4 / NA;   // value groups per A operand
@@ -580,9 +676,10 @@ __device__ __forceinline__ us2 vscale_max(const VScales<FAM, NA>& v) {
 // 16+4r+i of this lane's query) times the dequantized values; B operands:
 // tile nt (channels 16nt..16nt+15, column = col), token slots of quarter r.
 template <int FAM, int NA, int BV>
-__device__ __forceinline__ void vpart(const SlotPtrs& sp, const LaneOps& lo,
+__device__ __forceinline__ void vpart(const SlotPtrs& sp, const LaneOps<NA>& lo,
                                       const uint32_t (&P)[4], const VScales<FAM, NA>& vs,
-                                      const uint32_t* cst, WaveState<NA>& ws) {
+                                      const VWords<BV> (&vw)[8], const uint32_t* cst,
+                                      WaveState<NA>& ws) {
   constexpr int GPA = 4 / NA;   // value groups per A operand (KIVI)
   const int r = lo.r, col = lo.col;
   uint32_t P2[4];
@@ -601,19 +698,8 @@ __device__ __forceinline__ void vpart(const SlotPtrs& sp, const LaneOps& lo,
   for (int nt = 0; nt < 8; ++nt) {
     const int a = (FAM == RQ_KIVI) ? (nt / 2) / GPA : 0;
     uint32_t pr[4];
-    if constexpr (FAM == RQ_TURBO) {
-      const uint32_t* ch = sp.vc + (16 * nt + col) * BV;
-      if constexpr (BV == 3) {
-        const uint32_t z = lane_quarter3(ch, r);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pr[i] = tq_tab<3>((z >> (3 * i)) & pair_mask(3), lo.tabv);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pr[i] = tq_pair<BV>(ch, 4 * r + i, lo.lut1, lo.tabv);
-      }
-    } else {
-      vpairs<BV>(sp.vc + (16 * nt + col) * BV, r, pr);
-    }
+    if constexpr (FAM == RQ_TURBO) tq_vpairs<BV>(vw[nt], r, lo.lut1, lo.tabv, pr);
+    else vpairs<BV>(vw[nt], r, pr);
     ws.acc[nt] = mfma(make_h8(A[a][0], A[a][1], A[a][2], A[a][3]),
                       make_h8(pr[0], pr[1], pr[2], pr[3]), ws.acc[nt]);
   }
@@ -646,7 +732,7 @@ __device__ __forceinline__ void set_wv(int ev, uint32_t wv[4]) {
 // value-side scale of the block is at most 4094 * 2^Ev; rescale the wave's
 // sums accordingly.
 template <int FAM, int NA, int BV>
-__device__ __forceinline__ void block_rescale(const LaneOps& lo, float m_ref, float mx,
+__device__ __forceinline__ void block_rescale(const LaneOps<NA>& lo, float m_ref, float mx,
                                               us2 smax, f4& t0, f4& t1, WaveState<NA>& ws) {
   mx = __builtin_fmaxf(mx, xor_shfl(mx, 16));
   mx = __builtin_fmaxf(mx, xor_shfl(mx, 32));
@@ -689,7 +775,7 @@ __device__ __forceinline__ void block_rescale(const LaneOps& lo, float m_ref, fl
 
 // One block from the LDS slot: QK^T, online softmax, PV.
 template <int FAM, int NA, int BK, int BV>
-__device__ __forceinline__ void block_step(const uint8_t* slot, const LaneOps& lo,
+__device__ __forceinline__ void block_step(const uint8_t* slot, const LaneOps<NA>& lo,
                                            const uint32_t* cst, WaveState<NA>& ws) {
   constexpr int KF = key_fam(FAM), VF = val_fam(FAM);
   constexpr int MBK = meta_block_bytes(FAM, 0);
@@ -700,11 +786,16 @@ __device__ __forceinline__ void block_step(const uint8_t* slot, const LaneOps& l
   sp.vm = reinterpret_cast<const u4*>(slot + 512 * (BK + BV) + MBK);
   const float m_ref = ws.m_run == -INFINITY ? 0.0f : ws.m_run;
   f4 t0, t1;
-  kpart<KF, BK>(sp, lo, m_ref, t0, t1);
-  const VScales<VF, NA> vs = load_vscales<VF, NA>(sp, lo);
+  kpart<KF, NA, BK>(sp, lo, m_ref, t0, t1);
   // keep the phases apart: hoisting all LDS reads of the block to its top
-  // needs more registers than the waves per SIMD allow
+  // needs more registers than the waves per SIMD allow.  The value side's
+  // are issued here, ahead of the softmax, all at once (read one channel
+  // tile at a time they were waited for four times a block).
   __builtin_amdgcn_sched_barrier(0);
+  const VScales<VF, NA> vs = load_vscales<VF, NA>(sp, lo);
+  VWords<BV> vw[8];
+#pragma unroll
+  for (int nt = 0; nt < 8; ++nt) vw[nt] = load_vwords<BV>(sp.vc + (16 * nt + lo.col) * BV, lo.r);
   float mx = max3(t0[0], t1[0], t0[1]);
   mx = max3(mx, t1[1], t0[2]);
   mx = max3(mx, t1[2], t0[3]);
@@ -723,7 +814,7 @@ __device__ __forceinline__ void block_step(const uint8_t* slot, const LaneOps& l
     P[i] = as_u32(pv);
   }
   __builtin_amdgcn_sched_barrier(0);
-  vpart<VF, NA, BV>(sp, lo, P, vs, cst, ws);
+  vpart<VF, NA, BV>(sp, lo, P, vs, vw, cst, ws);
 }
 
 // A block's data is four contiguous byte ranges: K codes (512*BK), V codes
@@ -957,7 +1048,7 @@ __device__ __forceinline__ int claim_take(const Claims& cl, int lane, int n) {
 template <int FAM, int NA, int BK, int BV>
 __device__ __forceinline__ void stream_blocks(const Geo& g, int depth, int n_static, int n_up,
                                               int blk0, int stride, Claims& cl, int issued,
-                                              uint8_t* slots, const LaneOps& lo,
+                                              uint8_t* slots, const LaneOps<NA>& lo,
                                               const uint32_t* cst, WaveState<NA>& ws) {
   using S = Slot<FAM, BK, BV>;
   static_assert(kMaxDepth == 4, "the ring below rotates four marks");
@@ -1017,7 +1108,7 @@ __device__ __forceinline__ void stream_blocks(const Geo& g, int depth, int n_sta
 template <int FAM, int NA, int MAXB>
 __device__ __forceinline__ void dispatch(int bk, int bv, const Geo& g, int depth, int n_static,
                                          int n_up, int blk0, int stride, Claims& cl, int issued,
-                                         uint8_t* slots, const LaneOps& lo, const uint32_t* cst,
+                                         uint8_t* slots, const LaneOps<NA>& lo, const uint32_t* cst,
                                          WaveState<NA>& ws) {
 #define RQ_CASE(K, V)                                                              \
   case (K - 1) * 8 + (V - 1):                                                      \
@@ -1401,7 +1492,7 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
   issued += nb_ops;
   if (tid < 8) cst[tid] = tid < 4 ? kOnes : 0u;
   __syncthreads();
-  LaneOps lo;
+  LaneOps<NA> lo;
   lo.lane = lane;
   lo.r = lane >> 4;
   lo.col = lane & 15;
@@ -1488,6 +1579,7 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
     // and 32r + 16 + 4kb + k'
     const int8_t* kp = a.fpos.k[bk];
     const int8_t* vp = a.fpos.v[bv];
+    uint32_t qz[16];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -1497,8 +1589,23 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
         const h2 vh = {(_Float16)__builtin_ldexpf(q0, sh), (_Float16)__builtin_ldexpf(q1, sh)};
         const h2 vz = {(_Float16)__builtin_ldexpf(q0, -e), (_Float16)__builtin_ldexpf(q1, -e)};
         lo.qh[4 * kb + kk] = as_u32(vh);
-        lo.qz[4 * kb + kk] = as_u32(vz);
+        qz[4 * kb + kk] = as_u32(vz);
       }
+    if (key_fam(FAM) == RQ_KIVI) {
+      constexpr int RP = 4 / NA;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (NA < 4) lo.qm[NA < 4 ? i : 0] = (lo.gsub & 1) ? lo.qh[i] : 0u;
+#pragma unroll
+      for (int m = 0; m < NA; ++m)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          uint32_t v = qz[4 * m * RP + kk];
+#pragma unroll
+          for (int c = 1; c < RP; ++c) v = lo.gsub == c ? qz[4 * (m * RP + c) + kk] : v;
+          lo.qz[4 * m + kk] = v;
+        }
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) lo.vq[i] = h_pair((uint32_t)(15 + vp[i]) << 10);
     lo.corrK = (f4){0.f, 0.f, 0.f, 0.f};
@@ -1631,8 +1738,8 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
 // (quantized blocks: QuaRot and TurboQuant in the rotated domain) and the
 // nwin window slots win .. win+nwin-1 (original domain).  dst: a partial
 // slot to write the merged (max, sum, acc) to, or -1 to write the unit's
-// output.  Thread t owns E consecutive elements of one query row (E = 128 Gp
-// / 256, Gp the power of two >= G); up to kS slots are loaded at once, the
+// output.  Thread t owns E consecutive elements of one query row (128 G / E
+// <= 256); up to kS slots are loaded at once, the
 // missing ones as zeros, so that a merge of up to 16 slots is one latency.
 // Whole workgroup; lds: scratch of 128 G floats, plus the rotation
 // (TurboQuant, 32 KB).
@@ -1765,11 +1872,11 @@ __device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit,
 __device__ __forceinline__ void merge_slots(const AttnLaunch& a, size_t unit,
                                             __amdgpu_buffer_rsrc_t part, float* lds, int first,
                                             int count, int win, int nwin, int dst) {
-  if (a.GP <= 2)
+  if (a.G <= 2)
     merge_rows<1>(a, unit, part, lds, first, count, win, nwin, dst);
-  else if (a.GP <= 4)
+  else if (a.G <= 4)
     merge_rows<2>(a, unit, part, lds, first, count, win, nwin, dst);
-  else if (a.GP <= 8)
+  else if (a.G <= 8)
     merge_rows<4>(a, unit, part, lds, first, count, win, nwin, dst);
   else
     merge_rows<8>(a, unit, part, lds, first, count, win, nwin, dst);
@@ -1793,8 +1900,9 @@ __device__ __forceinline__ void reset_counter(uint64_t* counter, uint32_t epoch)
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// FAM: quantizer family; NA: A operands of the KIVI value side (G <= 4: 1,
-// G <= 8: 2, else 4); MAXB: largest bit-width handled (4 or 8).
+// FAM: quantizer family; NA: 16 / (4 GP) of the families with KIVI keys, GP
+// the columns a copy of the queries takes (G <= 4: 4, G <= 8: 8, else 16; NA
+// = 1, 2, 4), which is also the A operands of the KIVI value side; MAXB: largest bit-width handled (4 or 8).
 // The compiler allocates v0..v165 (the attribute's value is doubled for the
 // unified vector register file of this architecture: 83 -> 166);
 // v[166:167], the rest of the 168 that three workgroups per CU leave a

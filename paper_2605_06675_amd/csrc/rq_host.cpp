@@ -175,10 +175,17 @@ struct AttnShape {
   size_t lds;
 };
 
-bool attn_shape(const rq_cache* c, int max_blk_bytes, AttnShape* out) {
+//
+// TurboQuant layers of widths up to 4 start from two: their workgroups begin
+// with the rotation of the queries and are bound by LDS reads, which two
+// rings of more blocks serve as well as three, so fewer set-ups and partials
+// gain (4 x 8 units of 32768 tokens at 3 bits 56.7 -> 54.5 us, 4 of 24941 at
+// 3.5 bits 28.1 -> 26.1; with widths to 6, 8 units of 97088 lose: 50.2 ->
+// 52.6; KIVI 16 x 8 units of 8192 33.4 -> 36.2).
+bool attn_shape(const rq_cache* c, int max_blk_bytes, int max_bits, AttnShape* out) {
   const int G = c->n_q_heads / c->n_kv_heads;
   const size_t tail = rq::attention_tail_bytes(G, c->family);
-  for (int w = 3; w >= 1; --w) {
+  for (int w = c->family == RQ_TURBO && max_bits <= 4 ? 2 : 3; w >= 1; --w) {
     size_t share = (lds_per_cu() / w) / 2048 * 2048 - 64;
     share = share < lds_limit() ? share : lds_limit();
     if (share <= tail) continue;
@@ -315,8 +322,9 @@ rq_status decode_attention(const rq_cache* c, int32_t layer, int32_t n_tokens, c
     return fail(RQ_EINVAL, "NULL device pointer");
   if (!std::isfinite(scale)) return fail(RQ_EINVAL, "scale is not finite");
   const rq::LayerTable tab = layer_table(c, layer);
-  int max_blk = 0;
+  int max_blk = 0, max_bits = 0;
   for (int h = 0; h < c->n_kv_heads; ++h) {
+    for (int k = 0; k < 2; ++k) max_bits = tab.bits[h][k] > max_bits ? tab.bits[h][k] : max_bits;
     const int bb = 512 * (tab.bits[h][0] + tab.bits[h][1]) + meta_pair_bytes(c);
     max_blk = bb > max_blk ? bb : max_blk;
   }
@@ -339,7 +347,7 @@ rq_status decode_attention(const rq_cache* c, int32_t layer, int32_t n_tokens, c
     }
   }
   AttnShape shape;
-  if (!attn_shape(c, max_blk, &shape))
+  if (!attn_shape(c, max_blk, max_bits, &shape))
     return fail(RQ_EUNSUPPORTED,
                 "layer %d: two %d-byte blocks per wave do not fit the LDS of a CU "
                 "(K+V bit-widths of one kv-head are too wide)", layer, max_blk);
@@ -369,7 +377,8 @@ rq_status decode_attention(const rq_cache* c, int32_t layer, int32_t n_tokens, c
   a.B = c->batch;
   a.H = c->n_kv_heads;
   a.G = G;
-  a.GP = 1;
+  // (the kernels with KIVI keys have no layout for fewer than four)
+  a.GP = c->family == RQ_KIVI || c->family == RQ_KIVI_RTN ? 4 : 1;
   while (a.GP < G) a.GP *= 2;
   a.cap = c->capacity;
   a.R = c->residual;

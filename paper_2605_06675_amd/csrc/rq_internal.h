@@ -28,7 +28,10 @@ __host__ __device__ inline size_t meta_unit_offset(int family, int h, int kind, 
          (size_t)b * nblk_cap * (kind ? mv : mk);
 }
 constexpr int kAttnGroup = 16;        // streaming slots per merge group
-constexpr int kAttnMergeFlat = 16;    // at most this many: one merge level
+// At most this many slots: one merge level (24 slots in two rounds of loads
+// take less than a second ticket and merge: 57.6 -> 56.7 us at 4 x 8 units of
+// 24 TurboQuant slots).
+constexpr int kAttnMergeFlat = 32;
 constexpr int kAttnResChunk = 32;     // window tokens per window workgroup
 constexpr int kAttnMaxDepth = 4;      // most blocks in flight per attention wave
 constexpr int kAttnWaves = 4;         // waves per attention workgroup
@@ -102,7 +105,7 @@ struct AttnLaunch {
                           // one 128-byte line per claim group
   int claim_off;          // first claim counter of a unit (in counters)
   int B, H, G, cap, R;
-  int GP;                 // smallest power of two >= G
+  int GP;                 // smallest power of two >= G (KIVI keys: at least 4)
   int nq, n_tokens;
   int n_wg;               // grid slots per unit: the largest nwg[h]
   uint16_t nwg[RQ_MAX_KV_HEADS];  // workgroups streaming blocks, per kv-head
