@@ -98,40 +98,64 @@ __host__ __device__ __forceinline__ constexpr int stream3_pos(int i) {
   return 24 * ((i & 15) >> 2) + 3 * (i & 3) + (i >= 16 ? 12 : 0);
 }
 
-// Pack 32 codes (bytes, code i = byte i of c[i/4]) into B words.
+// Bytes (a0, b0, a2, b2), with (a1, b1, a3, b3) placed s bits above them.
+__device__ __forceinline__ uint32_t join_fields(uint32_t a, uint32_t b, int s) {
+  return __builtin_amdgcn_perm(b, a, 0x06020400u) |
+         (__builtin_amdgcn_perm(b, a, 0x07030501u) << s);
+}
+
+// Pack 32 codes (bytes, code i = byte i % 4 of c[i / 4]) into B words, four
+// codes i with their four codes i + 16 at a time.
 template <int B>
 __device__ __forceinline__ void pack_chunk(const uint32_t c[8], uint32_t out[B]) {
-  if constexpr (B == 3) {
-    out[0] = out[1] = out[2] = 0;
+  if constexpr (B == 8) {
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const uint32_t code = (c[i >> 2] >> (8 * (i & 3))) & 7u;
-      const int pos = stream3_pos(i), word = pos >> 5, bit = pos & 31;
-      out[word] |= code << bit;
-      if (bit > 29) out[word + 1] |= code >> (32 - bit);
+    for (int m = 0; m < 4; ++m) {
+      out[2 * m] = __builtin_amdgcn_perm(c[4 + m], c[m], 0x05040100u);
+      out[2 * m + 1] = __builtin_amdgcn_perm(c[4 + m], c[m], 0x07060302u);
     }
     return;
   } else {
-    int word = 0, shift = 0;
+    uint32_t ev[4], od[4];                 // codes 4m, 4m + 2 (+16), then the odd ones
 #pragma unroll
-    for (int p = 0; p < Planes<B>::n; ++p) {
-      const int w = Planes<B>::w[p];
-      const int per = 16 / w;
-      const uint32_t m = (1u << w) - 1u;
+    for (int m = 0; m < 4; ++m) {
+      ev[m] = __builtin_amdgcn_perm(c[4 + m], c[m], 0x06040200u);
+      od[m] = __builtin_amdgcn_perm(c[4 + m], c[m], 0x07050301u);
+    }
+    if constexpr (B == 3) {
+      uint32_t z[4];                       // the stream's quarters
 #pragma unroll
-      for (int d = 0; d < w; ++d) {
-        uint32_t acc = 0;
-#pragma unroll
-        for (int k = 0; k < per; ++k) {
-          const int i0 = d * per + k, i1 = 16 + d * per + k;
-          uint32_t c0 = (c[i0 >> 2] >> (8 * (i0 & 3))) & 0xffu;
-          uint32_t c1 = (c[i1 >> 2] >> (8 * (i1 & 3))) & 0xffu;
-          acc |= ((c0 >> shift) & m) << (k * w);
-          acc |= ((c1 >> shift) & m) << (16 + k * w);
-        }
-        out[word++] = acc;
+      for (int m = 0; m < 4; ++m) {
+        const uint32_t y = ev[m] | (od[m] << 3);
+        const uint32_t x = (y & 0x003f003fu) | ((y >> 2) & 0x0fc00fc0u);
+        z[m] = (x & 0xfffu) | ((x >> 4) & 0xfff000u);
       }
-      shift += w;
+      out[0] = z[0] | (z[1] << 24);
+      out[1] = (z[1] >> 8) | (z[2] << 16);
+      out[2] = (z[2] >> 16) | (z[3] << 8);
+    } else {
+      int word = 0, shift = 0;
+#pragma unroll
+      for (int p = 0; p < Planes<B>::n; ++p) {
+        const int w = Planes<B>::w[p];
+        const uint32_t mask = 0x01010101u * ((1u << w) - 1u);
+        uint32_t y[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+          y[m] = w == B ? ev[m] | (od[m] << w)
+                        : ((ev[m] >> shift) & mask) | (((od[m] >> shift) & mask) << w);
+        if (w == 4) {
+#pragma unroll
+          for (int m = 0; m < 4; ++m) out[word + m] = y[m];
+        } else if (w == 2) {
+          out[word] = join_fields(y[0], y[1], 4);
+          out[word + 1] = join_fields(y[2], y[3], 4);
+        } else {
+          out[word] = join_fields(join_fields(y[0], y[1], 2), join_fields(y[2], y[3], 2), 4);
+        }
+        word += w;
+        shift += w;
+      }
     }
   }
 }

@@ -22,24 +22,6 @@ __device__ __forceinline__ int pair_pos(int j) {
   return j < 16 ? 2 * j : 2 * (j - 16) + 1;
 }
 
-template <int B>
-__device__ __forceinline__ void store_words(uint32_t* dst, const uint32_t w[B]) {
-#pragma unroll
-  for (int i = 0; i < B; ++i) __builtin_nontemporal_store(w[i], dst + i);
-}
-
-template <int B>
-__device__ __forceinline__ void pack_store(const uint32_t c[8], uint32_t* dst) {
-  uint32_t w[B];
-  pack_chunk<B>(c, w);
-  store_words<B>(dst, w);
-}
-
-struct Smem {
-  uint32_t codes[kChunk * kD / 4];   // [32 tokens][128 channels] bytes
-  uint16_t meta[256];                // one block's metadata (512 B)
-};
-
 // ------------------------------------------------------------- KIVI (LDS)
 // Persistent kernel: every wave loops over blocks (block, kv-head, batch,
 // K|V in that order), with the next block's 8 KB already loading into
@@ -414,6 +396,73 @@ kivi_quant_kernel(QuantLaunch a) {
 // Per-token symmetric quantization over the token's 128 channels; QuaRot
 // (ROT = 1) first applies the orthonormal Hadamard rotation, RTN (ROT = 0)
 // quantizes the vector as it is.
+//
+// One wave a block, in two passes of 16 tokens.  Lane -> token 16 p + lane / 4
+// and quarter q = lane % 4, which is exactly packed chunk q of the token.  The
+// block's rows go to LDS as they lie in memory (whole rows per instruction),
+// each lane then reads its quarter: 16-byte piece s of token t lies in slot
+// s ^ (t % 4) of the row, so that the 16 lanes of a read's turn take all banks.
+//
+// Vector instructions bound this kernel (Qwen3-8B layer, 8 x 8 x 32768 tokens,
+// QuaRot at 4 bits: 265 us with the instruction count at 266 us of issue), then
+// memory.  Writing the lane-crossing butterflies as one instruction, leaving
+// the clamp out where the scale shows that it does nothing, one copy of the
+// rotation for all widths and a transpose of code bytes by 16 dword reads in
+// place of 64 byte reads: 233 us; whole-row copies to LDS with the loads' 32
+// registers freed: 228 us (5.9 TB/s of rows, codes and metadata).
+constexpr int kSymRow = kD / 2;              // dwords of a staged token
+constexpr int kSymPass = 16 * kSymRow;       // dwords of a pass
+constexpr int kSymCodes = kSymPass + 32;     // from pass 0's code bytes to pass 1's:
+                                             // half the banks apart
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// The block's rows into LDS, the first pass by the first four of eight copies.
+__device__ __forceinline__ void stage_rows(const QuantLaunch& a, int b, int h, int kind, int t0,
+                                           int lane, uint32_t* sm) {
+  const uint16_t* in = (kind ? a.v : a.k) + (size_t)(b * a.H + h) * a.n_new * kD;
+  const int g = lane >> 4, piece = (lane & 15) ^ g;     // of token 4 j + g
+  if (t0 >= a.n_past) {
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(in + (size_t)(t0 - a.n_past) * kD), 0, kChunk * kD * 2, 0x00020000);
+    if (a.stream) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kSymRow * j), 16,
+                                                 256 * g + 16 * piece, 1024 * j, 0, 2 /* NT */);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kSymRow * j), 16,
+                                                 256 * g + 16 * piece, 1024 * j, 0, 0);
+    }
+  } else {
+    // the row's address selects between the new input and the window
+    const int cap = a.R + kChunk;
+    const uint16_t* ring = a.resid + (((size_t)b * a.H + h) * 2 + kind) * cap * kD;
+    u4 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int t = t0 + 4 * j + g;
+      const uint16_t* row = t >= a.n_past ? in + (size_t)(t - a.n_past) * kD
+                                          : ring + (size_t)(t % cap) * kD;
+      x[j] = gptr(reinterpret_cast<const u4*>(row))[piece];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      *reinterpret_cast<u4*>(sm + 4 * kSymRow * j + 4 * lane) = x[j];
+  }
+}
+
+// Until at most N of the wave's copies are under way (the compiler does not
+// track the LDS they write).
+template <int N>
+__device__ __forceinline__ void wait_rows() {
+  static_assert(N < 16, "low bits of the count");
+  __builtin_amdgcn_s_waitcnt(N | (7 << 4));      // and all LDS operations
+  asm volatile("" ::: "memory");
+}
+
 __device__ __forceinline__ float dpp_xor1(float v) {
   // quad_perm [1,0,3,2]: exchange with lane ^ 1
   return __builtin_bit_cast(
@@ -428,172 +477,263 @@ __device__ __forceinline__ float dpp_xor2(float v) {
                                       0xF, true));
 }
 
-// One quarter of token t (channels 32 q .. 32 q + 31) into registers.
-// The row address selects between the new input and the residual window
-// without a branch around the loads (a divergent branch there would read
-// the input pointers with vector loads and wait for every load in flight).
-__device__ __forceinline__ void load_quarter(const QuantLaunch& a, int b, int h,
-                                             int kind, int t, int q, u4 raw[4]) {
-  const uint16_t* in = (kind ? a.v : a.k) + (size_t)(b * a.H + h) * a.n_new * kD;
-  const int cap = a.R + kChunk;
-  const uint16_t* ring = a.resid + (((size_t)b * a.H + h) * 2 + kind) * cap * kD;
-  const uint16_t* row = t >= a.n_past ? in + (size_t)(t - a.n_past) * kD
-                                      : ring + (size_t)(t % cap) * kD;
-  const RQ_GLOBAL u4* s = gptr(reinterpret_cast<const u4*>(row + 32 * q));
-#pragma unroll
-  for (int i = 0; i < 4; ++i) raw[i] = s[i];
+// v[i] + k * v[i] of lane ^ 1, then v[i] + k2 * v[i] of lane ^ 2.  (Written
+// out: the compiler keeps a move for every DPP operand.  Such an operand is
+// read at the earliest two instructions after it was written.)
+__device__ __forceinline__ void butterfly_quad(float v[8], float k1, float k2) {
+#define RQ_ST(CTRL, K)                                                                     \
+  "v_fmac_f32_dpp %0, %0, " K " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"      \
+  "v_fmac_f32_dpp %1, %1, " K " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"      \
+  "v_fmac_f32_dpp %2, %2, " K " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"      \
+  "v_fmac_f32_dpp %3, %3, " K " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"      \
+  "v_fmac_f32_dpp %4, %4, " K " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"      \
+  "v_fmac_f32_dpp %5, %5, " K " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"      \
+  "v_fmac_f32_dpp %6, %6, " K " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"      \
+  "v_fmac_f32_dpp %7, %7, " K " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+  asm("s_nop 1\n\t" RQ_ST("quad_perm:[1,0,3,2]", "%8") RQ_ST("quad_perm:[2,3,0,1]", "%9")
+      : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+        "+v"(v[7])
+      : "v"(k1), "v"(k2));
+#undef RQ_ST
 }
 
-// Write this block's packed V chunks from the staged code bytes: channel c
-// -> B words over the block's 32 tokens.
+// The rotation of a token held by a quad of lanes, this lane's quarter in v.
+// The butterflies keep their order (stride 1 .. 16 inside the lane, then 32
+// and 64 with lanes q ^ 1 and q ^ 2), so every value is the one that the
+// definition computes.  The upper lane of a pair takes other - own, the
+// lower one own + other: the caller has negated the inputs of the quarters
+// q = 1 and 2, which is exact and makes each of the two stages one fma with
+// a factor +-1 (the same single rounding of the same exact sum).
+__device__ __forceinline__ void rotate_quarter(float v[32], int q) {
+#pragma unroll
+  for (int hh = 1; hh < 32; hh *= 2)
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+      if ((i & hh) == 0) {
+        const float x = v[i], y = v[i + hh];
+        v[i] = x + y;
+        v[i + hh] = x - y;
+      }
+  const float k1 = (q & 1) ? 1.0f : -1.0f, k2 = (q & 2) ? 1.0f : -1.0f;
+#pragma unroll
+  for (int i = 0; i < 32; i += 8) butterfly_quad(v + i, k1, k2);
+  const float c = 0.08838834764831845f;  // fp32 nearest to 1/sqrt(128)
+#pragma unroll
+  for (int i = 0; i < 32; ++i) v[i] = v[i] * c;
+}
+
+// The largest magnitude of a token.  NAN_OUT: a NaN gives NaN, else it does
+// not count.
+template <bool NAN_OUT>
+__device__ __forceinline__ float quad_amax(const float v[32]) {
+  if constexpr (NAN_OUT) {
+    float m = vmax(__builtin_fabsf(v[0]), __builtin_fabsf(v[1]));
+#pragma unroll
+    for (int i = 2; i < 32; i += 2)
+      m = vmax(m, vmax(__builtin_fabsf(v[i]), __builtin_fabsf(v[i + 1])));
+    m = vmax(m, dpp_xor1(m));
+    return vmax(m, dpp_xor2(m));
+  } else {
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) m = __builtin_fmaxf(m, __builtin_fabsf(v[i]));
+    m = __builtin_fmaxf(m, dpp_xor1(m));
+    return __builtin_fmaxf(m, dpp_xor2(m));
+  }
+}
+
+// A scale whose rounding to fp16 is relative (normal, not saturated) or 0:
+// no quotient then exceeds (1 + 2^-11) q + 2^-20 < q + 1/2, q the largest
+// code, and none needs a clamp.
+__device__ __forceinline__ bool scale_exact(uint32_t s16) {
+  return s16 == 0u || (s16 >= 0x0400u && s16 < 0x7bffu);
+}
+
+// Scale of the token and 1 / scale.  Where a token of the wave has a scale
+// that is not exact in the above sense (or a NaN), all its values become
+// their clamped quotients (a NaN the lowest) and inv becomes 1.
+__device__ __forceinline__ uint32_t sym_scale(float v[32], float qm, float& inv) {
+  uint32_t s = f16_sat(quad_amax<true>(v) / qm);
+  const bool odd = __builtin_amdgcn_ballot_w64(!scale_exact(s)) != 0;
+  if (odd) s = f16_sat(quad_amax<false>(v) / qm);
+  const float sf = f16_to_f32((uint16_t)s);
+  inv = sf != 0.0f ? 1.0f / sf : 0.0f;
+  if (odd) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = __builtin_amdgcn_fmed3f(v[i] * inv, -qm, qm);
+    inv = 1.0f;
+  }
+  return s;
+}
+
+// Four codes as the bytes of a dword.
+__device__ __forceinline__ uint32_t code_bytes(const uint32_t cb[4]) {
+  return __builtin_amdgcn_perm(cb[1], cb[0], 0x0c0c0400u) |
+         __builtin_amdgcn_perm(cb[3], cb[2], 0x04000c0cu);
+}
+
+// cb: kMagicBits + code
 template <int B>
-__device__ __forceinline__ void pack_values_b(const Smem& sm, uint32_t* region_blk,
-                                              int lane) {
-  const uint8_t* cb = reinterpret_cast<const uint8_t*>(sm.codes);
+__device__ __forceinline__ void sym_key_chunk(const uint32_t cb[32], uint32_t* dst) {
+  if constexpr (B <= 4) {
+    ChunkAcc<B> acc;
+    acc.init();
 #pragma unroll
-  for (int rep = 0; rep < 2; ++rep) {
-    const int c = lane + rep * kWave;
-    uint32_t w[8];
+    for (int i = 0; i < 32; ++i) acc.add(i, cb[i]);
+    acc.finish();
+    store_chunk<B>(dst, acc.w);
+  } else {
+    uint32_t c[8], w[B];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      w[i] = (uint32_t)cb[(4 * i + 0) * kD + c] |
-             ((uint32_t)cb[(4 * i + 1) * kD + c] << 8) |
-             ((uint32_t)cb[(4 * i + 2) * kD + c] << 16) |
-             ((uint32_t)cb[(4 * i + 3) * kD + c] << 24);
-    }
-    pack_store<B>(w, region_blk + (size_t)c * B);
+    for (int i = 0; i < 8; ++i) c[i] = code_bytes(cb + 4 * i);
+    pack_chunk<B>(c, w);
+    store_chunk<B>(dst, w);
   }
 }
 
-// A block in two passes of 16 tokens; the second pass is loaded before the
-// first is computed.  Lane -> token 16 p + lane / 4 and quarter q = lane % 4,
-// which is exactly packed chunk q of the token.  The rotation's butterflies
-// keep their order (stride 1 .. 16 inside the lane, 32 and 64 with the
-// quad's lanes q ^ 1 and q ^ 2, each as one fma with a +-1 factor: the same
-// single rounding of the same exact sum), so every value is the one the
-// definition computes.  A code is rounded by one fp32 add of 2^23 + 2^(B-1)
-// to the clamped quotient: half-to-even on the integer grid, and the even
-// offset keeps the parity of ties, so the low bits hold rint(quotient) +
-// 2^(B-1).
-template <int ROT, int BF16, int B>
-__device__ __forceinline__ void sym_block(const QuantLaunch& a, Smem& sm, int b, int h,
-                                          int kind, int blk, int lane) {
-  constexpr int off = 1 << (B - 1);
-  constexpr float qm = (float)(off - 1);
-  constexpr float magic = 8388608.0f + (float)off;
-  const int t0 = blk * kChunk;
-  const int tq = lane >> 2, q = lane & 3;
-  uint32_t* region = reinterpret_cast<uint32_t*>(a.codes + a.tab.code_off[h][kind]);
-  u4 raw[2][4];
-  load_quarter(a, b, h, kind, t0 + tq, q, raw[0]);
-  load_quarter(a, b, h, kind, t0 + 16 + tq, q, raw[1]);
-#pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const int t = 16 * p + tq;
-    float v[32];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t ww[4] = {raw[p][i].x, raw[p][i].y, raw[p][i].z, raw[p][i].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[8 * i + 2 * e] = widen_t<BF16>(ww[e] & 0xffffu);
-        v[8 * i + 2 * e + 1] = widen_t<BF16>(ww[e] >> 16);
-      }
-    }
-    if constexpr (ROT) {
-#pragma unroll
-      for (int hh = 1; hh < 32; hh *= 2)
-#pragma unroll
-        for (int i = 0; i < 32; ++i)
-          if ((i & hh) == 0) {
-            const float x = v[i], y = v[i + hh];
-            v[i] = x + y;
-            v[i + hh] = x - y;
-          }
-      // stride 32: lane q ^ 1 holds channel c ^ 32; the lower half (q even)
-      // takes v + o, the upper half o - v
-      const float sg1 = (q & 1) ? -1.0f : 1.0f;
-#pragma unroll
-      for (int i = 0; i < 32; ++i) v[i] = __builtin_fmaf(sg1, v[i], dpp_xor1(v[i]));
-      // stride 64: lane q ^ 2 holds channel c ^ 64
-      const float sg2 = (q & 2) ? -1.0f : 1.0f;
-#pragma unroll
-      for (int i = 0; i < 32; ++i) v[i] = __builtin_fmaf(sg2, v[i], dpp_xor2(v[i]));
-      const float c = 0.08838834764831845f;  // fp32 nearest to 1/sqrt(128)
-#pragma unroll
-      for (int i = 0; i < 32; ++i) v[i] = v[i] * c;
-    }
-    float amax = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) amax = __builtin_fmaxf(amax, __builtin_fabsf(v[i]));
-    amax = __builtin_fmaxf(amax, dpp_xor1(amax));
-    amax = __builtin_fmaxf(amax, dpp_xor2(amax));
-    const uint16_t s16 = f16_sat(amax / qm);
-    const float sf = f16_to_f32(s16);
-    const float inv = (sf != 0.0f) ? 1.0f / sf : 0.0f;
-    if (q == 0) sm.meta[pair_pos(t)] = s16;
-    if (kind == 0) {
-      // keys: this lane's chunk packed from registers
-      ChunkAcc<B> acc;
-      acc.init();
-#pragma unroll
-      for (int i = 0; i < 32; ++i) {
-        const float r = __builtin_amdgcn_fmed3f(v[i] * inv, -qm, qm);
-        acc.add(i, __float_as_uint(r + magic));
-      }
-      acc.finish();
-      const size_t tok = (size_t)b * a.cap + t0 + t;
-      store_chunk<B>(region + (tok * 4 + q) * B, acc.w);
-    } else {
-      // values: code bytes staged as [token][channel] for the transpose
-      uint32_t* dst = sm.codes + (t * kD) / 4 + 8 * q;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        uint32_t cb[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          cb[e] = __float_as_uint(
-              __builtin_amdgcn_fmed3f(v[4 * i + e] * inv, -qm, qm) + magic);
-        dst[i] = __builtin_amdgcn_perm(cb[1], cb[0], 0x0c0c0400u) |
-                 __builtin_amdgcn_perm(cb[3], cb[2], 0x04000c0cu);
-      }
-    }
-  }
-  __syncthreads();
-  if (kind == 1) {
-    const int nblk_cap = a.cap / kChunk;
-    pack_values_b<B>(sm, region + ((size_t)b * nblk_cap + blk) * kD * B, lane);
-  }
+// Two adjacent channels' chunks from their code bytes.
+template <int B>
+__device__ __forceinline__ void sym_value_chunks(const uint32_t c[2][8], uint32_t* dst) {
+  uint32_t w[2 * B];
+  pack_chunk<B>(c[0], w);
+  pack_chunk<B>(c[1], w + B);
+  store_chunk<2 * B>(dst, w);
 }
 
 template <int ROT, int BF16>
 __global__ void __launch_bounds__(kWave)
 sym_quant_kernel(QuantLaunch a) {
-  __shared__ Smem sm;
+  __shared__ __attribute__((aligned(16))) uint32_t sm[2 * kSymPass];
   const int blk = a.blk0 + blockIdx.x;
   const int h = blockIdx.y;
   const int b = blockIdx.z / a.kind_n, kind = a.kind_lo + blockIdx.z % a.kind_n;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x, tq = lane >> 2, q = lane & 3;
+  const int nblk_cap = a.cap / kChunk, t0 = blk * kChunk;
+  stage_rows(a, b, h, kind, t0, lane, sm);
+  const int bits = kernarg_byte(&a.tab.bits[0][0], 2 * h + kind);
+  const int off = 1 << (bits - 1);
+  const float qm = (float)(off - 1);
+  // A code is rounded by one fp32 add of 2^23 + 2^(B-1) to the quotient:
+  // half-to-even on the integer grid, and the even offset keeps the parity
+  // of ties, so the low bits hold rint(quotient) + 2^(B-1).
+  const float magic = 8388608.0f + (float)off;
+  uint32_t* region = reinterpret_cast<uint32_t*>(a.codes + a.tab.code_off[h][kind]);
+  const uint32_t neg = (ROT && (q == 1 || q == 2)) ? 0x80008000u : 0u;
+  uint32_t scale[2];
+  wait_rows<4>();
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    float v[32];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u4 raw = *reinterpret_cast<const u4*>(
+          &sm[p * kSymPass + tq * kSymRow + 4 * ((4 * q + i) ^ (tq & 3))]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint32_t ww = raw[e];
+        if constexpr (ROT) {
+          ww ^= neg;
+          asm("" : "+v"(ww));    // (else negated per half)
+        }
+        v[8 * i + 2 * e] = widen_t<BF16>(ww & 0xffffu);
+        v[8 * i + 2 * e + 1] = widen_t<BF16>(ww >> 16);
+      }
+    }
+    if constexpr (ROT) rotate_quarter(v, q);
+    float inv;
+    scale[p] = sym_scale(v, qm, inv);
+    uint32_t cb[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) cb[i] = __float_as_uint(v[i] * inv + magic);
+    if (p == 0) wait_rows<0>();     // (here, not after the codes' stores)
+    if (kind == 0) {
+      // keys: this lane's chunk packed from registers
+      const size_t at = ((size_t)b * a.cap + t0 + 16 * p + tq) * 4 + q;
+#define RQ_CASE(NB) \
+  case NB: sym_key_chunk<NB>(cb, region + at * NB); break;
+      switch (bits) {
+        RQ_CASE(2)
+        RQ_CASE(3)
+        RQ_CASE(4)
+        RQ_CASE(5)
+        RQ_CASE(6)
+        RQ_CASE(7)
+        RQ_CASE(8)
+        default: break;
+      }
+#undef RQ_CASE
+    } else {
+      // values: code bytes staged as [token][channel] for the transpose, in
+      // place of the rows read above (a wave's LDS operations keep their
+      // order); the
+      // two 16-byte stores of a lane are exchanged for two tokens in four, so
+      // that the 16 lanes of a store's turn take all banks
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        u4 d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = code_bytes(cb + 16 * i + 4 * e);
+        const int at = 8 * q + 4 * (i ^ ((tq >> 1) & 1));
+        *reinterpret_cast<u4*>(&sm[p * kSymCodes + tq * (kD / 4) + at]) = d;
+      }
+    }
+  }
   if (a.ring_fused)
     copy_window(a.ring, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
                 gridDim.x * gridDim.y * gridDim.z, lane);
-  switch (kernarg_byte(&a.tab.bits[0][0], 2 * h + kind)) {
-    case 2: sym_block<ROT, BF16, 2>(a, sm, b, h, kind, blk, lane); break;
-    case 3: sym_block<ROT, BF16, 3>(a, sm, b, h, kind, blk, lane); break;
-    case 4: sym_block<ROT, BF16, 4>(a, sm, b, h, kind, blk, lane); break;
-    case 5: sym_block<ROT, BF16, 5>(a, sm, b, h, kind, blk, lane); break;
-    case 6: sym_block<ROT, BF16, 6>(a, sm, b, h, kind, blk, lane); break;
-    case 7: sym_block<ROT, BF16, 7>(a, sm, b, h, kind, blk, lane); break;
-    default: sym_block<ROT, BF16, 8>(a, sm, b, h, kind, blk, lane); break;
+  if (q == 0) {
+    // tokens t and t + 16: a pair of the metadata's order
+    uint32_t* m = reinterpret_cast<uint32_t*>(
+        a.meta + meta_unit_offset(a.family, h, kind, b, a.B, nblk_cap) +
+        (size_t)blk * kMetaBlockTok);
+    __builtin_nontemporal_store(scale[0] | (scale[1] << 16), gptr(m) + tq);
   }
-  __syncthreads();
-  // metadata of this block
-  const int nblk_cap = a.cap / kChunk;
-  uint8_t* m = a.meta + meta_unit_offset(a.family, h, kind, b, a.B, nblk_cap) +
-               (size_t)blk * kMetaBlockTok;
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(sm.meta);
-  if (lane < kMetaBlockTok / 4)
-    __builtin_nontemporal_store(src[lane], reinterpret_cast<uint32_t*>(m) + lane);
+  if (kind == 0) return;
+  __builtin_amdgcn_wave_barrier();
+  // Lane -> the tokens of pass lane / 32 and channels 4 (lane % 32) .. + 3;
+  // after the exchange of the wave's halves, all tokens of two channels.
+  const int hf = lane >> 5, col = lane & 31;
+  uint32_t tr[4][4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    uint32_t r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int t = 4 * m + e;
+      r[e] = sm[hf * kSymCodes + t * (kD / 4) + (((t >> 1) & 1) ? col ^ 4 : col)];
+    }
+    const uint32_t a01 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u);
+    const uint32_t b01 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
+    const uint32_t a23 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u);
+    const uint32_t b23 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+    tr[0][m] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
+    tr[1][m] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
+    tr[2][m] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
+    tr[3][m] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
+  }
+  uint32_t c[2][8];
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const auto x = __builtin_amdgcn_permlane32_swap(tr[k][m], tr[2 + k][m], false, false);
+      c[k][m] = x[0];
+      c[k][4 + m] = x[1];
+    }
+  const size_t at = ((size_t)b * nblk_cap + blk) * kD + 4 * col + 2 * hf;
+#define RQ_CASE(NB) \
+  case NB: sym_value_chunks<NB>(c, region + at * NB); break;
+  switch (bits) {
+    RQ_CASE(2)
+    RQ_CASE(3)
+    RQ_CASE(4)
+    RQ_CASE(5)
+    RQ_CASE(6)
+    RQ_CASE(7)
+    RQ_CASE(8)
+    default: break;
+  }
+#undef RQ_CASE
 }
 
 __global__ void __launch_bounds__(kWave)
@@ -636,10 +776,19 @@ hipError_t launch_kivi(const QuantLaunch& q, hipStream_t s) {
   return hipGetLastError();
 }
 
+// A launch that reads more than this marks its loads non-temporal: they pass
+// by the caches, which then keep what the rest of the program uses.  Below it
+// the input, just written by the projections, is likely still in the 256 MiB
+// of last-level cache and plain loads find it there.  (RTN 4 bits, 8 kv-heads,
+// plain / non-temporal: 32 MiB 8.76 / 9.15 us, 64 MiB 15.5 / 16.6, 128 MiB
+// 31.7 / 30.5, 256 MiB 63.0 / 60.9, 512 MiB 123.3 / 119.0.)
+constexpr size_t kStreamBytes = (size_t)96 << 20;
+
 // per-token symmetric blocks (QuaRot with the rotation, RTN without) of
 // kinds q.kind_lo .. + q.kind_n - 1
-hipError_t launch_sym(const QuantLaunch& q, bool rot, hipStream_t s) {
+hipError_t launch_sym(QuantLaunch q, bool rot, hipStream_t s) {
   dim3 grid(q.nblk, q.H, q.B * q.kind_n);
+  q.stream = (size_t)q.nblk * q.H * q.B * q.kind_n * (kChunk * kD * 2) > kStreamBytes;
   // bit-widths of the symmetric quantizers are 2..8 (checked on the host)
   if (rot && q.is_bf16)
     hipLaunchKernelGGL((sym_quant_kernel<1, 1>), grid, dim3(kWave), 0, s, q);

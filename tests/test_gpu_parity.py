@@ -402,3 +402,55 @@ def test_llama3_8b_layer_sampled():
     print(f"llama3-8b layer attention max-abs error {worst:.3e}")
     assert worst < ATOL
     assert np.all(np.isfinite(out))
+
+
+@pytest.mark.parametrize("family", [workloads.QUAROT, workloads.RTN])
+@pytest.mark.parametrize("dtype", [workloads.F16, workloads.BF16])
+def test_symmetric_scales_at_the_fp16_limits(family, dtype):
+    """Tokens whose scale is zero, subnormal or saturated next to ordinary
+    ones, at every width, with blocks whose rows come from the window, from
+    the new tokens and from both."""
+    torch = _torch()
+    H, T, R = 7, 32 * 5 + 9, 32
+    bits = np.array([[[2 + h, 8 - h] for h in range(H)]], dtype=np.uint8)
+    rng = np.random.default_rng(11)
+    x = rng.standard_normal((2, H, T, 128)).astype(np.float32)
+    top = 1.5e4 if dtype == workloads.F16 else 1e30
+    for i, m in enumerate([0.0, 1e-7, 6e-6, 2e-4, 4e-3, top, 300.0]):
+        x[0, :, 3 + 11 * i::83] *= m
+        x[1, :, 5 + 9 * i::71] *= m
+    if dtype == workloads.F16:
+        u16 = x.astype(np.float16).view(np.uint16)
+    else:
+        u16 = torch.from_numpy(x).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+    K, V = (gh.dev(u16[k][None], dtype) for k in (0, 1))
+    kvc = rq.KVCache(family, dtype, 1, 1, H, 4 * H, 192, R, bits)
+    t0 = 0
+    for n in (45, 1, 50, T - 96):
+        kvc.append(0, K[:, :, t0:t0 + n].contiguous(), V[:, :, t0:t0 + n].contiguous())
+        t0 += n
+    torch.cuda.synchronize()
+    _check_cache(family, dtype, kvc, u16[0][None], u16[1][None], bits, R, 1, H, T)
+
+
+@pytest.mark.parametrize("family", [workloads.QUAROT, workloads.RTN])
+def test_symmetric_large_launch_equals_small_ones(family):
+    """A launch that reads more than 96 MiB (non-temporal loads) against the
+    same tokens in launches that read less."""
+    torch = _torch()
+    B, H, T = 4, 8, 32 * 193
+    bits = np.array([[[2 + h % 7, 2 + (h + 3) % 7] for h in range(H)]], dtype=np.uint8)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    K, V = (torch.randn((B, H, T, 128), generator=g, device="cuda").to(torch.bfloat16)
+            for _ in range(2))
+    got = []
+    for chunks in ([T], [32 * 96, 32 * 97]):
+        kvc = rq.KVCache(family, workloads.BF16, 1, B, H, 4 * H, T, 0, bits)
+        t0 = 0
+        for n in chunks:
+            kvc.append(0, K[:, :, t0:t0 + n].contiguous(), V[:, :, t0:t0 + n].contiguous())
+            t0 += n
+        torch.cuda.synchronize()
+        got.append(gh.read_buffers(kvc))
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
