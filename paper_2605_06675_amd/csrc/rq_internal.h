@@ -74,7 +74,8 @@ struct QuantLaunch {
   int is_bf16;
   int family;
   int n_cu;               // compute units of the device (grid sizing)
-  int stream;             // the launch reads more than the caches hold (set by it)
+  int stream;             // set by the launch: it reads more than the caches hold,
+  int by_batch;           // the order of its workgroups
   const uint16_t* rot;    // TurboQuant: this layer's rotations [H][128][128] bf16
   const float* cb;        // TurboQuant: codebook table (rq_turbo_codebook)
   LayerTable tab;

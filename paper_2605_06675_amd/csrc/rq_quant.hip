@@ -3,9 +3,9 @@
 // (batch entry, kv-head, K|V) unit; the unit's bit-width and code region come
 // from the per-layer table in the kernel arguments.
 //
-// The KIVI block is staged once in LDS.  Group statistics run along one
-// axis of the block and packing along the other (keys: statistics per
-// channel over the 32 tokens, chunks of 32 channels per token; values: the
+// The block's rows are copied straight to LDS.  KIVI's group statistics run
+// along one axis of the block and packing along the other (keys: statistics
+// per channel over the 32 tokens, chunks of 32 channels per token; values: the
 // reverse), so each phase reads the rows or columns it needs from LDS and
 // every code goes straight into its packed word.
 #include "rq_device.h"
@@ -22,23 +22,103 @@ __device__ __forceinline__ int pair_pos(int j) {
   return j < 16 ? 2 * j : 2 * (j - 16) + 1;
 }
 
+struct BlockId {
+  int blk, h, b, kind;
+};
+
+// The block of a workgroup (see set_grid).
+__device__ __forceinline__ BlockId block_id(const QuantLaunch& a) {
+  int blk = blockIdx.x, y = blockIdx.y, b = blockIdx.z;
+  if (!a.by_batch) {
+    b = blockIdx.x / (unsigned)a.nblk;
+    blk -= b * a.nblk;
+  }
+  if (a.by_batch) {
+    const int k = y >= a.H;
+    return {a.blk0 + blk, y - k * a.H, b, a.kind_lo + k};
+  }
+  const int both = a.kind_n == 2;
+  return {a.blk0 + blk, y >> both, b, a.kind_lo + (both ? y & 1 : 0)};
+}
+
+// ---------------------------------------------------------------- staging
+typedef __attribute__((address_space(3))) void lds_void;
+
+// A block's rows go to LDS as they lie in memory (whole rows per instruction),
+// 16-byte piece s of token t in slot s ^ (t % 8) of the row: the 16 lanes of a
+// 16-byte read's turn then take all banks wherever they read one piece of
+// eight tokens (two pieces apart by 8) or four pieces of four tokens.
+constexpr int kRow = kD / 2;                 // dwords of a staged token
+constexpr int kPass = 16 * kRow;             // dwords of 16 tokens
+__device__ __forceinline__ int slot(int t, int piece) {     // dword of the piece
+  return t * kRow + 4 * (piece ^ (t & 7));
+}
+
+// The block's rows into LDS, the first 16 tokens by the first four of eight copies.
+__device__ __forceinline__ void stage_rows(const QuantLaunch& a, int b, int h, int kind, int t0,
+                                           int lane, uint32_t* sm) {
+  const uint16_t* in = (kind ? a.v : a.k) + (size_t)(b * a.H + h) * a.n_new * kD;
+  const int g = lane >> 4;
+  const int piece[2] = {(lane & 15) ^ g, (lane & 15) ^ g ^ 4};   // of token 4 j + g
+  if (t0 >= a.n_past) {                                  // the same for the wave
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(in + (size_t)(t0 - a.n_past) * kD), 0, kChunk * kD * 2, 0x00020000);
+    if (a.stream) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kRow * j), 16,
+                                                 256 * g + 16 * piece[j & 1], 1024 * j, 0, 2 /* NT */);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kRow * j), 16,
+                                                 256 * g + 16 * piece[j & 1], 1024 * j, 0, 0);
+    }
+  } else {
+    // the row's address selects between the new input and the window
+    const int cap = a.R + kChunk;
+    const uint16_t* ring = a.resid + (((size_t)b * a.H + h) * 2 + kind) * cap * kD;
+    u4 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int t = t0 + 4 * j + g;
+      const uint16_t* row = t >= a.n_past ? in + (size_t)(t - a.n_past) * kD
+                                          : ring + (size_t)(t % cap) * kD;
+      x[j] = gptr(reinterpret_cast<const u4*>(row))[piece[j & 1]];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      *reinterpret_cast<u4*>(sm + 4 * kRow * j + 4 * lane) = x[j];
+  }
+}
+
+// Until at most N of the wave's copies are under way (the compiler does not
+// track the LDS they write).
+template <int N>
+__device__ __forceinline__ void wait_rows() {
+  static_assert(N < 16, "low bits of the count");
+  __builtin_amdgcn_s_waitcnt(N | (7 << 4));      // and all LDS operations
+  asm volatile("" ::: "memory");
+}
+
+// The launch's window rows (called when the wave's own rows are staged).
+__device__ __forceinline__ void copy_ring(const QuantLaunch& a, const BlockId& id, int lane) {
+  if (a.ring_fused)
+    copy_window(a.ring, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
+                gridDim.x * gridDim.y * gridDim.z, lane);
+}
+
 // ------------------------------------------------------------- KIVI (LDS)
-// Persistent kernel: every wave loops over blocks (block, kv-head, batch,
-// K|V in that order), with the next block's 8 KB already loading into
-// registers while the current one is quantized from the wave's own LDS
-// area.  The waves of a workgroup share nothing, so no
-// workgroup barrier is needed: a wave's LDS operations complete in issue
-// order.
-constexpr int kQWaves = 4;                // waves per workgroup
-constexpr int kQBuf = 1;                  // register buffers per wave
-// workgroups per CU: three when every width of the layer is at most 4 bits
-// (the code paths then fit 168 registers), else two
-__host__ __device__ constexpr int quant_occupancy(int maxb) { return maxb <= 4 ? 3 : 2; }
-constexpr int kRowW = 68;                 // dwords per staged row (272 B)
+// One wave a block: no barrier is needed, as a wave's LDS operations complete
+// in issue order.  Memory bounds this kernel, so what counts is the bytes in
+// flight: 16 waves a CU with 8 KB each (LDS bounds them: 9.6 KB a wave), a new
+// wave's copies starting as soon as one ends.  Llama-3-8B layer, 16 x 8 x 8192
+// tokens at 2.5 bits: 128 us with 12 persistent waves a CU that loaded the next
+// block into registers, 108 us so (6.1 TB/s of rows, codes and metadata).
 constexpr int kTabE = 34;                 // float2 entries per table row
 
 struct KiviSmem {
-  uint32_t x[kChunk * kRowW];             // [token][channel pair]
+  uint32_t x[kChunk * kRow];              // the rows, pieces as slot() places them
   float2 tab[4 * kTabE];                  // (zero, 1/scale): K [chunk][channel],
                                           // V [group][token]
   uint16_t meta[256];                     // the block's metadata (512 B)
@@ -140,50 +220,6 @@ __device__ __forceinline__ void store_chunk(uint32_t* dst, const uint32_t* w) {
   for (int i = 0; i < B; ++i) __builtin_nontemporal_store(w[i], g + i);
 }
 
-struct BlockId {
-  int blk, h, b, kind;
-};
-
-__device__ __forceinline__ BlockId block_id(const QuantLaunch& a, int it) {
-  BlockId id;
-  id.blk = a.blk0 + it % a.nblk;
-  const int r = it / a.nblk;
-  id.h = r % a.H;
-  const int z = r / a.H;
-  id.b = z / a.kind_n;
-  id.kind = a.kind_lo + z % a.kind_n;
-  return id;
-}
-
-// Global -> registers: the block's 32 token rows, 16 bytes per lane and
-// step (step j, lane l: token 4 j + l / 16, bytes 16 (l % 16) of the row).
-// Branch-free: each row's address selects between the new input and the
-// residual window, so that every block issues the same eight loads.  The
-// loads are non-temporal: every byte is read once.
-__device__ __forceinline__ void load_block(const QuantLaunch& a, const BlockId& id,
-                                           u4 v[8], int lane) {
-  const int t0 = id.blk * kChunk;
-  const uint16_t* in = (id.kind ? a.v : a.k) + (size_t)(id.b * a.H + id.h) * a.n_new * kD;
-  const int cap = a.R + kChunk;
-  const uint16_t* ring = a.resid + (((size_t)id.b * a.H + id.h) * 2 + id.kind) * cap * kD;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int c = j * kWave + lane, t = t0 + (c >> 4), p = c & 15;
-    const uint16_t* row = t >= a.n_past ? in + (size_t)(t - a.n_past) * kD
-                                        : ring + (size_t)(t % cap) * kD;
-    v[j] = __builtin_nontemporal_load(gptr(reinterpret_cast<const u4*>(row)) + p);
-  }
-}
-
-__device__ __forceinline__ void stage_block(KiviSmem& sm, const u4 v[8], int lane) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int c = j * kWave + lane, t = c >> 4, p = c & 15;
-    *reinterpret_cast<u4*>(&sm.x[t * kRowW + 4 * p]) = v[j];
-  }
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Metadata of the block, staged in LDS, to its 512-byte slot.
 __device__ __forceinline__ void store_meta(const QuantLaunch& a, const KiviSmem& sm,
                                            const BlockId& id, int lane) {
@@ -204,7 +240,7 @@ __device__ __forceinline__ void kivi_keys_lds(const QuantLaunch& a, KiviSmem& sm
   float mn0 = INFINITY, mx0 = -INFINITY, mn1 = INFINITY, mx1 = -INFINITY;
 #pragma unroll
   for (int t = 0; t < kChunk; ++t) {
-    const uint32_t w = sm.x[t * kRowW + lane];
+    const uint32_t w = sm.x[t * kRow + (lane ^ (4 * (t & 7)))];
     const float x0 = lo16<BF16>(w), x1 = hi16<BF16>(w);
     mn0 = vmin(mn0, x0);
     mx0 = vmax(mx0, x0);
@@ -248,8 +284,8 @@ __device__ __forceinline__ void kivi_keys_lds(const QuantLaunch& a, KiviSmem& sm
         zf[2 * i + 1] = e.z;
         inv[2 * i + 1] = e.w;
       }
-      const u4* row = reinterpret_cast<const u4*>(&sm.x[t * kRowW + 16 * q + 8 * half]);
-      const u4 d0 = row[0], d1 = row[1];
+      const u4 d0 = *reinterpret_cast<const u4*>(&sm.x[slot(t, 4 * q + 2 * half)]);
+      const u4 d1 = *reinterpret_cast<const u4*>(&sm.x[slot(t, 4 * q + 2 * half + 1)]);
       const uint32_t w[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -276,11 +312,10 @@ __device__ __forceinline__ void kivi_values_lds(const QuantLaunch& a, KiviSmem& 
 #pragma unroll
     for (int g2 = 0; g2 < 2; ++g2) {
       const int g = 2 * hb + g2;
-      const u4* row = reinterpret_cast<const u4*>(&sm.x[t * kRowW + 16 * g]);
       float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const u4 d = row[i];
+        const u4 d = *reinterpret_cast<const u4*>(&sm.x[slot(t, 4 * g + i)]);
         const uint32_t w[4] = {d.x, d.y, d.z, d.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -318,7 +353,7 @@ __device__ __forceinline__ void kivi_values_lds(const QuantLaunch& a, KiviSmem& 
 #pragma unroll
     for (int tt = 0; tt < 16; ++tt) {
       const int t = 16 * half + tt;
-      const uint32_t w = sm.x[t * kRowW + lane];
+      const uint32_t w = sm.x[t * kRow + (lane ^ (4 * (t & 7)))];
       acc0.add(t, kivi_code_bits<B>(lo16<BF16>(w), zf[tt], inv[tt]));
       acc1.add(t, kivi_code_bits<B>(hi16<BF16>(w), zf[tt], inv[tt]));
     }
@@ -359,37 +394,18 @@ __device__ __forceinline__ void kivi_block(const QuantLaunch& a, KiviSmem& sm,
 #undef RQ_KIVI_CASE
 }
 
-// Block cur from the buffer v, whose registers then start loading the
-// wave's next block.  Every step issues the same loads (past the last
-// block, a copy of the last one, never used), so that the compiler's wait
-// before a buffer's staging counts the younger buffers' loads on every path
-// and leaves them in flight.
+// MAXB: the widest bit-width of the launch (4 or 8: up to 4 the code paths fit
+// the 128 registers that four waves a SIMD leave)
 template <int BF16, int MAXB>
-__device__ __forceinline__ void kivi_step(const QuantLaunch& a, KiviSmem& sm, int cur,
-                                          int stride, int total, u4 v[8], int lane) {
-  stage_block(sm, v, lane);
-  const int nxt = cur + kQBuf * stride;
-  load_block(a, block_id(a, nxt < total ? nxt : total - 1), v, lane);
-  kivi_block<BF16, MAXB>(a, sm, block_id(a, cur), lane);
-  __builtin_amdgcn_wave_barrier();
-}
-
-// MAXB: the widest bit-width of the layer (4 or 8)
-template <int BF16, int MAXB>
-__global__ void __launch_bounds__(kQWaves * kWave, quant_occupancy(MAXB))
+__global__ void __launch_bounds__(kWave, MAXB <= 4 ? 4 : 3)
 kivi_quant_kernel(QuantLaunch a) {
-  __shared__ KiviSmem smem[kQWaves];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & (kWave - 1);
-  KiviSmem& sm = smem[wave];
-  const int total = a.nblk * a.H * a.B * a.kind_n;
-  const int stride = gridDim.x * kQWaves;
-  int it = blockIdx.x * kQWaves + wave;
-  if (a.ring_fused) copy_window(a.ring, it, stride, lane);
-  if (it >= total) return;
-  u4 v[8];
-  load_block(a, block_id(a, it), v, lane);
-  for (; it < total; it += stride) kivi_step<BF16, MAXB>(a, sm, it, stride, total, v, lane);
+  __shared__ __attribute__((aligned(16))) KiviSmem sm;
+  const int lane = threadIdx.x;
+  const BlockId id = block_id(a);
+  stage_rows(a, id.b, id.h, id.kind, id.blk * kChunk, lane, sm.x);
+  wait_rows<0>();
+  kivi_block<BF16, MAXB>(a, sm, id, lane);
+  copy_ring(a, id, lane);
 }
 
 // ------------------------------------------------------- QuaRot and RTN
@@ -399,9 +415,7 @@ kivi_quant_kernel(QuantLaunch a) {
 //
 // One wave a block, in two passes of 16 tokens.  Lane -> token 16 p + lane / 4
 // and quarter q = lane % 4, which is exactly packed chunk q of the token.  The
-// block's rows go to LDS as they lie in memory (whole rows per instruction),
-// each lane then reads its quarter: 16-byte piece s of token t lies in slot
-// s ^ (t % 4) of the row, so that the 16 lanes of a read's turn take all banks.
+// block's rows go to LDS, each lane then reads its quarter.
 //
 // Vector instructions bound this kernel (Qwen3-8B layer, 8 x 8 x 32768 tokens,
 // QuaRot at 4 bits: 265 us with the instruction count at 266 us of issue), then
@@ -410,58 +424,8 @@ kivi_quant_kernel(QuantLaunch a) {
 // rotation for all widths and a transpose of code bytes by 16 dword reads in
 // place of 64 byte reads: 233 us; whole-row copies to LDS with the loads' 32
 // registers freed: 228 us (5.9 TB/s of rows, codes and metadata).
-constexpr int kSymRow = kD / 2;              // dwords of a staged token
-constexpr int kSymPass = 16 * kSymRow;       // dwords of a pass
-constexpr int kSymCodes = kSymPass + 32;     // from pass 0's code bytes to pass 1's:
+constexpr int kSymCodes = kPass + 32;        // from pass 0's code bytes to pass 1's:
                                              // half the banks apart
-
-typedef __attribute__((address_space(3))) void lds_void;
-
-// The block's rows into LDS, the first pass by the first four of eight copies.
-__device__ __forceinline__ void stage_rows(const QuantLaunch& a, int b, int h, int kind, int t0,
-                                           int lane, uint32_t* sm) {
-  const uint16_t* in = (kind ? a.v : a.k) + (size_t)(b * a.H + h) * a.n_new * kD;
-  const int g = lane >> 4, piece = (lane & 15) ^ g;     // of token 4 j + g
-  if (t0 >= a.n_past) {
-    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(in + (size_t)(t0 - a.n_past) * kD), 0, kChunk * kD * 2, 0x00020000);
-    if (a.stream) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kSymRow * j), 16,
-                                                 256 * g + 16 * piece, 1024 * j, 0, 2 /* NT */);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kSymRow * j), 16,
-                                                 256 * g + 16 * piece, 1024 * j, 0, 0);
-    }
-  } else {
-    // the row's address selects between the new input and the window
-    const int cap = a.R + kChunk;
-    const uint16_t* ring = a.resid + (((size_t)b * a.H + h) * 2 + kind) * cap * kD;
-    u4 x[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int t = t0 + 4 * j + g;
-      const uint16_t* row = t >= a.n_past ? in + (size_t)(t - a.n_past) * kD
-                                          : ring + (size_t)(t % cap) * kD;
-      x[j] = gptr(reinterpret_cast<const u4*>(row))[piece];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      *reinterpret_cast<u4*>(sm + 4 * kSymRow * j + 4 * lane) = x[j];
-  }
-}
-
-// Until at most N of the wave's copies are under way (the compiler does not
-// track the LDS they write).
-template <int N>
-__device__ __forceinline__ void wait_rows() {
-  static_assert(N < 16, "low bits of the count");
-  __builtin_amdgcn_s_waitcnt(N | (7 << 4));      // and all LDS operations
-  asm volatile("" ::: "memory");
-}
 
 __device__ __forceinline__ float dpp_xor1(float v) {
   // quad_perm [1,0,3,2]: exchange with lane ^ 1
@@ -603,10 +567,9 @@ __device__ __forceinline__ void sym_value_chunks(const uint32_t c[2][8], uint32_
 template <int ROT, int BF16>
 __global__ void __launch_bounds__(kWave)
 sym_quant_kernel(QuantLaunch a) {
-  __shared__ __attribute__((aligned(16))) uint32_t sm[2 * kSymPass];
-  const int blk = a.blk0 + blockIdx.x;
-  const int h = blockIdx.y;
-  const int b = blockIdx.z / a.kind_n, kind = a.kind_lo + blockIdx.z % a.kind_n;
+  __shared__ __attribute__((aligned(16))) uint32_t sm[2 * kPass];
+  const BlockId id = block_id(a);
+  const int blk = id.blk, h = id.h, b = id.b, kind = id.kind;
   const int lane = threadIdx.x, tq = lane >> 2, q = lane & 3;
   const int nblk_cap = a.cap / kChunk, t0 = blk * kChunk;
   stage_rows(a, b, h, kind, t0, lane, sm);
@@ -627,7 +590,7 @@ sym_quant_kernel(QuantLaunch a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const u4 raw = *reinterpret_cast<const u4*>(
-          &sm[p * kSymPass + tq * kSymRow + 4 * ((4 * q + i) ^ (tq & 3))]);
+          &sm[slot(16 * p + tq, 4 * q + i)]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         uint32_t ww = raw[e];
@@ -678,9 +641,7 @@ sym_quant_kernel(QuantLaunch a) {
       }
     }
   }
-  if (a.ring_fused)
-    copy_window(a.ring, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
-                gridDim.x * gridDim.y * gridDim.z, lane);
+  copy_ring(a, id, lane);
   if (q == 0) {
     // tokens t and t + 16: a pair of the metadata's order
     uint32_t* m = reinterpret_cast<uint32_t*>(
@@ -750,18 +711,35 @@ ring_kernel(RingLaunch a) {
   dst[threadIdx.x] = src[threadIdx.x];
 }
 
+// A launch that reads more than this marks its loads non-temporal: they pass
+// by the caches, which then keep what the rest of the program uses.  Below it
+// the input, just written by the projections, is likely still in the 256 MiB
+// of last-level cache and plain loads find it there.  (RTN 4 bits, 8 kv-heads,
+// plain / non-temporal: 32 MiB 8.76 / 9.15 us, 64 MiB 15.5 / 16.6, 128 MiB
+// 31.7 / 30.5, 256 MiB 63.0 / 60.9, 512 MiB 123.3 / 119.0.)
+constexpr size_t kStreamBytes = (size_t)96 << 20;
+
+
+// Workgroups in order of the blocks of a unit, then the kv-heads and kinds of
+// a batch entry (the inputs' order), or, for units of at least 6144 tokens,
+// the batch entries of a head and kind (the codes' order, and one width at a
+// time): KIVI 2.5 bits, 8 kv-heads, by batch / by head, us: 16 x 2048 tokens
+// 31.2 / 32.9, 64 x 2048 114.1 / 122.5, 16 x 4096 58.8 / 58.5, 32 x 4096
+// 113.3 / 114.0, 11 x 8192 80.7 / 78.8, 16 x 8192 115.5 / 107.9, 16 x 16384
+// 225.9 / 212.7.
+dim3 set_grid(QuantLaunch& q) {
+  q.stream = (size_t)q.nblk * q.H * q.B * q.kind_n * (kChunk * kD * 2) > kStreamBytes;
+  q.by_batch = q.nblk < 192 && q.B <= 65535;      // (the grid's limit along z)
+  return q.by_batch ? dim3(q.nblk, q.H * q.kind_n, q.B) : dim3(q.nblk * q.B, q.H * q.kind_n);
+}
+
 // KIVI blocks of kinds q.kind_lo .. + q.kind_n - 1
-hipError_t launch_kivi(const QuantLaunch& q, hipStream_t s) {
+hipError_t launch_kivi(QuantLaunch q, hipStream_t s) {
   int maxb = 1;
   for (int h = 0; h < q.H; ++h)
     for (int k = q.kind_lo; k < q.kind_lo + q.kind_n; ++k)
       maxb = q.tab.bits[h][k] > maxb ? q.tab.bits[h][k] : maxb;
-  // persistent: as many workgroups of kQWaves waves as fit on the device
-  const long waves = (long)q.nblk * q.H * q.B * q.kind_n;
-  long wg = (waves + kQWaves - 1) / kQWaves;
-  const long cap = (long)(q.n_cu > 0 ? q.n_cu : 256) * quant_occupancy(maxb);
-  if (wg > cap) wg = cap;
-  dim3 grid((unsigned)wg), block(kQWaves * kWave);
+  const dim3 grid = set_grid(q), block(kWave);
   if (maxb <= 4) {
     if (q.is_bf16)
       hipLaunchKernelGGL((kivi_quant_kernel<1, 4>), grid, block, 0, s, q);
@@ -776,19 +754,10 @@ hipError_t launch_kivi(const QuantLaunch& q, hipStream_t s) {
   return hipGetLastError();
 }
 
-// A launch that reads more than this marks its loads non-temporal: they pass
-// by the caches, which then keep what the rest of the program uses.  Below it
-// the input, just written by the projections, is likely still in the 256 MiB
-// of last-level cache and plain loads find it there.  (RTN 4 bits, 8 kv-heads,
-// plain / non-temporal: 32 MiB 8.76 / 9.15 us, 64 MiB 15.5 / 16.6, 128 MiB
-// 31.7 / 30.5, 256 MiB 63.0 / 60.9, 512 MiB 123.3 / 119.0.)
-constexpr size_t kStreamBytes = (size_t)96 << 20;
-
 // per-token symmetric blocks (QuaRot with the rotation, RTN without) of
 // kinds q.kind_lo .. + q.kind_n - 1
 hipError_t launch_sym(QuantLaunch q, bool rot, hipStream_t s) {
-  dim3 grid(q.nblk, q.H, q.B * q.kind_n);
-  q.stream = (size_t)q.nblk * q.H * q.B * q.kind_n * (kChunk * kD * 2) > kStreamBytes;
+  const dim3 grid = set_grid(q);
   // bit-widths of the symmetric quantizers are 2..8 (checked on the host)
   if (rot && q.is_bf16)
     hipLaunchKernelGGL((sym_quant_kernel<1, 1>), grid, dim3(kWave), 0, s, q);

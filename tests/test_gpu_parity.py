@@ -433,8 +433,8 @@ def test_symmetric_scales_at_the_fp16_limits(family, dtype):
     _check_cache(family, dtype, kvc, u16[0][None], u16[1][None], bits, R, 1, H, T)
 
 
-@pytest.mark.parametrize("family", [workloads.QUAROT, workloads.RTN])
-def test_symmetric_large_launch_equals_small_ones(family):
+@pytest.mark.parametrize("family", [workloads.KIVI, workloads.QUAROT, workloads.RTN])
+def test_large_launch_equals_small_ones(family):
     """A launch that reads more than 96 MiB (non-temporal loads) against the
     same tokens in launches that read less."""
     torch = _torch()
@@ -454,3 +454,26 @@ def test_symmetric_large_launch_equals_small_ones(family):
         got.append(gh.read_buffers(kvc))
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+def test_kivi_orders_of_workgroups():
+    """Units of 191 and 192 blocks (the line between the two orders) in one
+    launch against the same tokens in launches of fewer blocks."""
+    torch = _torch()
+    B, H = 3, 2
+    bits = np.array([[[1, 3], [4, 2]]], dtype=np.uint8)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    K, V = (torch.randn((B, H, 192 * 32, 128), generator=g, device="cuda").to(torch.float16)
+            for _ in range(2))
+    for T in (191 * 32, 192 * 32):
+        got = []
+        for chunks in ([T], [32 * 90, T - 32 * 90]):
+            kvc = rq.KVCache(workloads.KIVI, workloads.F16, 1, B, H, H, T, 0, bits)
+            t0 = 0
+            for n in chunks:
+                kvc.append(0, K[:, :, t0:t0 + n].contiguous(), V[:, :, t0:t0 + n].contiguous())
+                t0 += n
+            torch.cuda.synchronize()
+            got.append(gh.read_buffers(kvc))
+        for a, b in zip(*got):
+            np.testing.assert_array_equal(a, b)
