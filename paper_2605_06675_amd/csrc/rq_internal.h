@@ -60,6 +60,11 @@ struct RingLaunch {
   int t_lo, t_hi;         // tokens [t_lo, t_hi) go to the window
 };
 
+// A quantize launch copies the window rows: any wave, as no block reads a ring
+// slot that they take; or, for each (batch entry, kv-head, kind), the wave of
+// its first block, the only one that reads the ring.
+enum { kRingAny = 1, kRingFirst = 2 };
+
 struct QuantLaunch {
   const uint16_t* k;      // [B][H][n_new][128]
   const uint16_t* v;
@@ -70,7 +75,7 @@ struct QuantLaunch {
   int blk0, nblk;         // blocks [blk0, blk0 + nblk) get quantized
   int kind_lo, kind_n;    // kinds kind_lo .. kind_lo + kind_n - 1 (K = 0, V = 1)
   RingLaunch ring;        // window rows this launch also copies
-  int ring_fused;         // (when set; else the window has its own launch)
+  int ring_fused;         // how (0: the window has its own launch; kRing..)
   int is_bf16;
   int family;
   int n_cu;               // compute units of the device (grid sizing)

@@ -29,7 +29,22 @@ struct BlockId {
 // The block of a workgroup (see set_grid).
 __device__ __forceinline__ BlockId block_id(const QuantLaunch& a) {
   int blk = blockIdx.x, y = blockIdx.y, b = blockIdx.z;
-  if (!a.by_batch) {
+  if (a.ring_fused == kRingFirst) {
+    // the first blocks of all units start first: their waves have the window
+    // to copy as well (11 x 8 units of 64 blocks: 29.0 us with them in place)
+    const unsigned ys = a.H * a.kind_n, units = ys * a.B;
+    const unsigned i = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const unsigned rest = a.nblk > 1 ? a.nblk - 1 : 1, j = i - units;
+    const unsigned unit = i < units ? i : j / rest;
+    blk = i < units ? 0 : 1 + j - unit * rest;
+    if (a.by_batch) {
+      b = unit / ys;
+      y = unit - b * ys;
+    } else {
+      y = unit / (unsigned)a.B;
+      b = unit - y * a.B;
+    }
+  } else if (!a.by_batch) {
     b = blockIdx.x / (unsigned)a.nblk;
     blk -= b * a.nblk;
   }
@@ -103,9 +118,11 @@ __device__ __forceinline__ void wait_rows() {
 
 // The launch's window rows (called when the wave's own rows are staged).
 __device__ __forceinline__ void copy_ring(const QuantLaunch& a, const BlockId& id, int lane) {
-  if (a.ring_fused)
+  if (a.ring_fused == kRingAny)
     copy_window(a.ring, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
                 gridDim.x * gridDim.y * gridDim.z, lane);
+  else if (a.ring_fused == kRingFirst && id.blk == a.blk0)
+    copy_unit_window(a.ring, id.b, id.h, id.kind, lane);
 }
 
 // ------------------------------------------------------------- KIVI (LDS)
@@ -785,7 +802,7 @@ hipError_t launch_quantize(const QuantLaunch& a, hipStream_t s) {
     hipError_t e = launch_kivi(q, s);
     if (e != hipSuccess) return e;
     q.kind_lo = 1;
-    q.ring_fused = 0;   // copied by the keys' launch
+    if (q.ring_fused == kRingAny) q.ring_fused = 0;   // copied by the keys' launch
     return launch_sym(q, false, s);
   }
   return launch_sym(q, a.family == RQ_QUAROT, s);

@@ -28,4 +28,27 @@ __device__ __forceinline__ void copy_window(const RingLaunch& r, int worker, int
   }
 }
 
+// The window rows of one (batch entry, kv-head, kind), by the wave that has
+// read every row of its old window that still had to be quantized: eight
+// rows' loads (32 rows) at a time.
+__device__ __forceinline__ void copy_unit_window(const RingLaunch& r, int b, int h, int kind,
+                                                 int lane) {
+  const int nt = r.t_hi - r.t_lo, cap = r.R + kChunk;
+  const size_t bh = (size_t)b * r.H + h;
+  const uint16_t* src = (kind ? r.v : r.k) + (bh * r.n_new + (r.t_lo - r.n_past)) * kD;
+  uint16_t* dst = r.resid + (bh * 2 + kind) * cap * kD;
+  const int p = lane & 15;
+  for (int base = lane >> 4; base < nt; base += 32) {
+    u4 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (base + 4 * j < nt)
+        x[j] = gptr(reinterpret_cast<const u4*>(src + (size_t)(base + 4 * j) * kD))[p];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (base + 4 * j < nt)
+        gptr(reinterpret_cast<u4*>(dst + (size_t)((r.t_lo + base + 4 * j) % cap) * kD))[p] = x[j];
+  }
+}
+
 }  // namespace rq

@@ -456,6 +456,22 @@ def test_large_launch_equals_small_ones(family):
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("family", [workloads.KIVI, workloads.QUAROT, workloads.RTN,
+                                    workloads.KIVI_RTN])
+@pytest.mark.parametrize("R", [0, 32, 96])
+def test_chunked_window_copies(family, R):
+    """Chunks whose window rows take ring slots that no block, one block or
+    several blocks of the same append still read, with one and many blocks a
+    unit, against the oracle on all tokens."""
+    torch = _torch()
+    B, H, dtype = 2, 3, workloads.F16
+    chunks = [32, 64, 64, 32, 33, 63, 100, 31, 1, 224, 7, 65, 128]
+    T = sum(chunks)
+    bits = np.array([[[3, 4], [2, 5], [4, 2]]], dtype=np.uint8)
+    kvc, ks, vs, _ = _build(family, dtype, H, 2, T, R, bits, batch=B, chunks=chunks)
+    _check_cache(family, dtype, kvc, ks, vs, bits, R, B, H, T)
+
+
 def test_kivi_orders_of_workgroups():
     """Units of 191 and 192 blocks (the line between the two orders) in one
     launch against the same tokens in launches of fewer blocks."""
