@@ -47,11 +47,6 @@ __device__ __forceinline__ float f16_to_f32(uint16_t b) {
   return (float)__builtin_bit_cast(_Float16, b);
 }
 
-// rint half-to-even of a value already clamped to [lo, hi] (|v| < 2^22).
-__device__ __forceinline__ int rint_i(float v) {
-  return (int)__builtin_rintf(v);
-}
-
 // Asymmetric group parameters from (min, max): zero = fp16(min), scale =
 // fp16(max(max - zero, 0) / qmax); inv = 1/scale (0 when scale == 0, which
 // sends every code to 0).
@@ -70,13 +65,6 @@ __device__ __forceinline__ AsymParams asym_params(float mn, float mx,
   float sf = f16_to_f32(p.s16);
   p.inv = (sf != 0.0f) ? 1.0f / sf : 0.0f;
   return p;
-}
-
-__device__ __forceinline__ int asym_code(float x, const AsymParams& p,
-                                         float qmax) {
-  float r = (x - p.zf) * p.inv;  // two roundings: built with fp-contract off
-  r = __builtin_fminf(__builtin_fmaxf(r, 0.0f), qmax);
-  return rint_i(r);
 }
 
 // Bit planes of a b-bit code, widest first (three-bit codes are single

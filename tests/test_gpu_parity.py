@@ -357,6 +357,22 @@ def test_calibration_sweep(family, bits):
         np.testing.assert_allclose(b, wb, rtol=1e-4)
 
 
+@pytest.mark.parametrize("family", [workloads.KIVI, workloads.QUAROT, workloads.RTN])
+@pytest.mark.parametrize("blocks", [1, 15, 33])
+def test_calibration_sweep_block_counts(family, blocks):
+    """Sums over fewer blocks than the reduction loads at once, and more."""
+    _torch()
+    dtype, bits = workloads.BF16, [2, 3, 8]
+    x16 = workloads.calib_cpu(4, 32 * blocks, dtype)
+    x = workloads.u16_to_f32(x16, dtype)
+    for is_value, sl in ((0, slice(0, 2)), (1, slice(2, 4))):
+        mse = rq.rq_calibrate_distortion(
+            family, dtype, gh.dev(np.ascontiguousarray(x16[sl]), dtype), is_value, bits)[0]
+        want = ocalib.sweep(family, x[sl], bits, bool(is_value))
+        tol = np.array([2.0 ** (bb - 21) for bb in bits])
+        assert np.all(np.abs(mse / want - 1) <= tol[None, :])
+
+
 # --------------------------------------------- full-size layer, sampled units
 def test_llama3_8b_layer_sampled():
     """One full layer of the Llama-3-8B shaped workload (batch 16, 8192

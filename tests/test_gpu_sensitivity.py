@@ -59,3 +59,10 @@ def test_calibration_sized_with_cap_and_allocation():
     beta = np.random.default_rng(4).uniform(3.6, 5.3, size=64)
     bits, _, _ = rq.rq_allocate_bits(wc, np.ones(64), beta, 3.0, 2, 6)
     assert bits.sum() == 192
+
+
+@pytest.mark.parametrize("S,T", [(64, 8), (65, 8), (43, 300)])
+def test_partials_around_one_wave(S, T):
+    # 64, 65 and (two chunks a slab, the sequence split over rounds) 86 partials
+    w, want = _run(rq.RQ_F32, _grads(S, 2, T, 5))
+    np.testing.assert_allclose(w, want, rtol=RTOL)
