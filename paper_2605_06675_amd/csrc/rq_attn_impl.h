@@ -5,7 +5,8 @@
 // workgroup; a unit is one (batch, kv-head).  Slots 0 .. nwg[h]-1 stream the
 // quantized 32-token blocks of their unit (about three workgroups per CU in
 // all, each kv-head's share sized by the cost of its widths); the first
-// slots first attend to the 16-bit residual window, 32 tokens each.  Each workgroup
+// slots first attend to the 16-bit residual window, 32 tokens each (or, where
+// the chip has room for them, workgroups of their own do).  Each workgroup
 // writes a partial (max, sum, acc) with cache-coherent stores and takes a
 // ticket from a per-unit counter; the last to arrive merges the unit's
 // partials and writes the output (QuaRot: rotated back).  A wave streams every
