@@ -1288,7 +1288,9 @@ __device__ __forceinline__ void ld_part(__amdgpu_buffer_rsrc_t p, uint32_t off, 
 // Tokens t_lo .. t_hi-1 (at most 32) of the 16-bit residual window of one
 // unit, original domain, to partial `slot`.  One pass from registers: all
 // rows are loaded at once; Q K^T on the matrix cores from the 16-bit rows as
-// they are (exact products, fp32 sums), each wave computing all scores;
+// they are (exact products, fp32 sums; for a softmax scale far from 1 the
+// bf16 queries times 2^wexp, so that no sum leaves the fp32 range: see
+// AttnLaunch), each wave computing all scores;
 // P V in fp32, wave w taking channels 32 w .. 32 w + 31, with the
 // probabilities passed between lanes through plds, 2 KiB of the wave's own
 // LDS.  The token this call appends is read from the new input and written
@@ -1330,6 +1332,16 @@ __device__ __forceinline__ void window_chunk_t(const AttnLaunch& a, int b, int h
     const RQ_GLOBAL u4* r = (const RQ_GLOBAL u4*)(gptr(a.q) + (unit * a.G + (col < a.G ? col : 0)) * kD);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) qx[ks] = r[4 * ks + g];
+    if (BF16 && a.wexp != 0)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t w = qx[ks][e];
+          const float lo = __builtin_ldexpf(__uint_as_float(w << 16), a.wexp);
+          const float hi = __builtin_ldexpf(__uint_as_float(w & 0xffff0000u), a.wexp);
+          qx[ks][e] = (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
+        }
   }
 #pragma unroll
   for (int k = 0; k < 8; ++k)
@@ -1349,7 +1361,7 @@ __device__ __forceinline__ void window_chunk_t(const AttnLaunch& a, int b, int h
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      p[tt][i] = 16 * tt + 4 * g + i < n ? d[i] * a.qscale : -INFINITY;
+      p[tt][i] = 16 * tt + 4 * g + i < n ? d[i] * a.wscale : -INFINITY;
       m = __builtin_fmaxf(m, p[tt][i]);
     }
   }

@@ -391,6 +391,11 @@ rq_status decode_attention(const rq_cache* c, int32_t layer, int32_t n_tokens, c
   a.is_bf16 = c->dtype == RQ_BF16;
   a.family = c->family;
   a.qscale = scale * 1.4426950408889634f;
+  if (c->dtype == RQ_BF16 && std::isfinite(a.qscale)) {
+    std::frexp(a.qscale, &a.wexp);
+    if (a.wexp >= -7 && a.wexp <= 30) a.wexp = 0;
+  }
+  a.wscale = std::ldexp(a.qscale, -a.wexp);
   if (c->family == RQ_TURBO) {
     a.rot = static_cast<const uint16_t*>(c->rotation) +
             (size_t)layer * c->n_kv_heads * rq::kD * rq::kD;

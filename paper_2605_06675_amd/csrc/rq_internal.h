@@ -122,6 +122,13 @@ struct AttnLaunch {
   int area_bytes;         // LDS bytes of the ring/merge/staging area
   int is_bf16, family;
   float qscale;           // scale * log2(e)
+  // The window's scores are (2^wexp q) . k times wscale = qscale 2^-wexp.
+  // bf16 queries below 2^56 / scale and keys below 2^56 have sums below
+  // 2^(120.6 - e), e the exponent of qscale (0.5 <= qscale 2^-e < 1): wexp is
+  // 0 for e = -7 .. 30 (above it products would fall among the subnormals)
+  // and e beyond; fp16 sums always fit.
+  int wexp;
+  float wscale;
   const uint16_t* rot;    // TurboQuant: this layer's rotations [H][128][128] bf16
   const float* cb;        // TurboQuant: codebook table (rq_turbo_codebook)
   LayerTable tab;

@@ -158,3 +158,32 @@ def test_large_value_scales_at_some_tokens(family, bits, phase):
         want = oatt.decode_attention(q, u.keys(), v_hat)
         err = np.max(np.abs(out[b, h * G:(h + 1) * G] - want))
         assert err < gp.attention_tol(v_hat), (b, h, err)
+
+
+@pytest.mark.parametrize("q_exp", [122, 44, -121])
+def test_scales_far_from_one(q_exp):
+    # queries around 2^q_exp and a scale that brings them back to 2^-3: the
+    # raw products of the 16-bit window's rows leave fp32's range (q_exp 122;
+    # 44 is inside it on both sides) or fall among its least normal numbers
+    # (-121), while scale * q is ordinary, for the window and for the blocks
+    import torch
+    from oracle import attention as oatt
+    scale = 2.0 ** (-3 - q_exp)
+    bits = np.array([[[2, 2], [3, 2], [4, 3], [8, 5]]])
+    rng = np.random.default_rng(13)
+    kf = 8.0 * rng.standard_normal((BATCH, H, T, 128))
+    kvc, ks, vs = _fill(workloads.KIVI, workloads.BF16, bits, kf, rng.standard_normal(kf.shape))
+    units = gp._check_cache(workloads.KIVI, workloads.BF16, kvc, ks, vs, bits, R, BATCH, H, T)
+    q16 = workloads.bits16_from_f32(
+        (rng.standard_normal((BATCH, H * G, 128)) * 2.0 ** q_exp).astype(np.float32),
+        workloads.BF16)
+    out = kvc.attention(0, gh.dev(q16, workloads.BF16), scale=scale)
+    torch.cuda.synchronize()
+    out = out.cpu().numpy()
+    assert np.all(np.isfinite(out))
+    for (b, h), u in units.items():
+        q = workloads.u16_to_f32(q16[b, h * G:(h + 1) * G], workloads.BF16).astype(np.float64)
+        v_hat = u.values()
+        want = oatt.decode_attention(q, u.keys(), v_hat, scale)
+        err = np.max(np.abs(out[b, h * G:(h + 1) * G] - want))
+        assert err < gp.attention_tol(v_hat), (b, h, err)
