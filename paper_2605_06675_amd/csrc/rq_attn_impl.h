@@ -1344,8 +1344,11 @@ __device__ __forceinline__ void window_chunk_t(const AttnLaunch& a, int b, int h
         }
   }
 #pragma unroll
-  for (int k = 0; k < 8; ++k)
+  for (int k = 0; k < 8; ++k) {
     vx[k] = ((const RQ_GLOBAL uint32_t*)row(vb, vn, 8 * g + k))[16 * wave + col];
+    // (an infinity of the last token must not meet the probability 0 there)
+    vx[k] = 8 * g + k < n ? vx[k] : 0u;
+  }
   // scores: lane = query col, tokens 16 tt + 4g + i
   float p[2][4], m = -INFINITY, l = 0.0f;
 #pragma unroll

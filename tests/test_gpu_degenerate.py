@@ -187,3 +187,23 @@ def test_scales_far_from_one(q_exp):
         want = oatt.decode_attention(q, u.keys(), v_hat, scale)
         err = np.max(np.abs(out[b, h * G:(h + 1) * G] - want))
         assert err < gp.attention_tol(v_hat), (b, h, err)
+
+
+@pytest.mark.parametrize("T_win", [1, 21, 32, 45])
+def test_infinite_value_of_the_last_window_token(T_win):
+    # an infinity in the newest token's values shows in its own channel only:
+    # the places behind it, up to a whole chunk of 32, have no part in it
+    import torch
+    dtype = workloads.F16
+    rng = np.random.default_rng(14)
+    kf, vf = rng.standard_normal((2, 1, 2, T_win, 128))
+    vf[:, :, -1, 5] = np.inf
+    k16, v16 = (workloads.bits16_from_f32(x, dtype) for x in (kf, vf))
+    kvc = rq.KVCache(workloads.KIVI, dtype, 1, 1, 2, 2 * G, 64, 64, np.array([[[2, 2], [3, 3]]]))
+    kvc.append(0, gh.dev(k16, dtype), gh.dev(v16, dtype))
+    q16 = workloads.bits16_from_f32(rng.standard_normal((1, 2 * G, 128)), dtype)
+    out = kvc.attention(0, gh.dev(q16, dtype))
+    torch.cuda.synchronize()
+    out = out.cpu().numpy()
+    assert np.all(out[:, :, 5] == np.inf)
+    assert np.all(np.isfinite(np.delete(out, 5, axis=2)))
