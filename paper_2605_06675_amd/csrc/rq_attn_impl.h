@@ -571,9 +571,11 @@ __device__ __forceinline__ void kpart(const SlotPtrs& sp, const LaneOps<NA>& lo,
     float x = X[0];
     if constexpr (RP == 4) {
       // replica rho = lo.gsub: the diagonal element, then the four replicas
+      // (opposite ones first: every replica then adds the same two sums, and
+      // all hold the same bits, which what follows relies on)
       x = (lo.gsub & 2) ? ((lo.gsub & 1) ? X[3] : X[2]) : ((lo.gsub & 1) ? X[1] : X[0]);
-      x += row_ror<4>(x);
       x += row_ror<8>(x);
+      x += row_ror<4>(x);
     } else if constexpr (RP == 2) {
       x = (lo.gsub & 1) ? X[1] : X[0];
       x += row_ror<8>(x);

@@ -207,3 +207,30 @@ def test_infinite_value_of_the_last_window_token(T_win):
     out = out.cpu().numpy()
     assert np.all(out[:, :, 5] == np.inf)
     assert np.all(np.isfinite(np.delete(out, 5, axis=2)))
+
+
+@pytest.mark.parametrize("group", [1, 4, 6, 16])
+def test_equal_values_give_equal_channels(group):
+    # the query replicas behind the four 32-channel groups of KIVI's values
+    # hold the same probabilities to the bit, so values that are equal over
+    # the channels give outputs that are; keys with outlier channels make the
+    # zero-point sums large, whose order would otherwise show (many units, so
+    # that a wave has several blocks under one running maximum)
+    import torch
+    dtype, batch, heads, tokens = workloads.F16, 128, 4, 1024
+    rng = np.random.default_rng(15)
+    kf = rng.standard_normal((heads, tokens, 128))
+    kf[..., 7::16] += 3000.0 * np.abs(rng.standard_normal((heads, 1, 8)))
+    vf = np.broadcast_to(rng.choice([-2.0, -1.0, 0.5, 3.0], (heads, tokens, 1)), kf.shape)
+    K, V = (gh.dev(workloads.bits16_from_f32(np.ascontiguousarray(x), dtype), dtype)[None]
+            .expand(batch, heads, tokens, 128).contiguous() for x in (kf, vf))
+    kvc = rq.KVCache(workloads.KIVI, dtype, 1, batch, heads, heads * group, tokens, 0,
+                     np.array([[[2, 2], [4, 3], [3, 1], [6, 5]]]))
+    kvc.append(0, K, V)
+    q16 = workloads.bits16_from_f32(
+        np.abs(rng.standard_normal((batch, heads * group, 128))), dtype)
+    out = kvc.attention(0, gh.dev(q16, dtype))
+    torch.cuda.synchronize()
+    out = out.cpu().numpy()
+    assert np.all(np.isfinite(out))
+    np.testing.assert_array_equal(out, np.broadcast_to(out[..., :1], out.shape))
