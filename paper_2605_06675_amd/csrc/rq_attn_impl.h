@@ -1222,34 +1222,38 @@ __device__ __forceinline__ void rotate_queries(const AttnLaunch& a, const TurboP
 }
 
 // Partial results.  Slot of a unit: float acc[G][128], then (max, sum)[G].
-// Slots of a unit: 0 .. nw-1 streaming, nw .. nw+n_rw-1 the window, then the
-// group partials of the two-level merge.  Stored and loaded through a buffer
-// resource of the unit's slots, 16 bytes an instruction, with the sc1 bit:
-// agent scope, coherent across the GPU's L2 caches, so that the workgroup
-// that merges a unit's partials sees the other workgroups' results without a
-// cache flush.  (As single-dword atomics of the same scope the loads of a
-// merge of 16 slots at G = 8 took 8.3 us of the long-context launch's 49.)
-// A load at kNoSlot, beyond the resource, returns zeros: a slot of sum 0.
+// Slots of a unit: 0 .. nw-1 streaming, then the group partials of a two-level
+// merge, then the window's: what one merge reads lies side by side.  Stored
+// and loaded through a buffer resource of one slot or of the slots of a round
+// of loads (a whole unit's can exceed 4 GiB: 32 window tokens have a slot), 16
+// bytes an instruction, with the sc1 bit: agent scope, coherent across the
+// GPU's L2 caches, so that the workgroup that merges a unit's partials sees
+// the other workgroups' results without a cache flush.  (As single-dword
+// atomics of the same scope the loads of a merge of 16 slots at G = 8 took 8.3
+// us of the long-context launch's 49.)  Loads beyond the resource, such as at
+// kNoSlot, return zeros: a slot of sum 0.
 constexpr int kAgentScope = 16;   // cache policy bit sc1
 constexpr uint32_t kNoSlot = 0x7fffff00u;
 
-__device__ __forceinline__ uint32_t part_slot(const AttnLaunch& a, int slot) {
-  return (uint32_t)slot * (uint32_t)a.G * ((2 + kD) * sizeof(float));
+__device__ __forceinline__ uint32_t part_bytes(const AttnLaunch& a) {
+  return (uint32_t)a.G * ((2 + kD) * sizeof(float));
 }
-__device__ __forceinline__ uint32_t part_acc(uint32_t slot_off, int row, int c) {
-  return slot_off + (uint32_t)(row * kD + c) * sizeof(float);
+__device__ __forceinline__ uint32_t part_acc(int row, int c) {
+  return (uint32_t)(row * kD + c) * sizeof(float);
 }
-__device__ __forceinline__ uint32_t part_ml(const AttnLaunch& a, uint32_t slot_off, int row) {
-  return slot_off + (uint32_t)(a.G * kD + 2 * row) * sizeof(float);
+__device__ __forceinline__ uint32_t part_ml(const AttnLaunch& a, int row) {
+  return (uint32_t)(a.G * kD + 2 * row) * sizeof(float);
 }
-// (made anew where it is used: kept over the block loop it would cost the
-// widest variants registers they spill)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t part_of(const AttnLaunch& a, size_t unit) {
+// Slots slot .. slot + n - 1 of a unit.  (Made anew where it is used: kept over
+// the block loop it would cost the widest variants registers they spill.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t part_of(const AttnLaunch& a, size_t unit,
+                                                          int slot, int n = 1) {
   uint32_t u = (uint32_t)unit;
   asm volatile("" : "+v"(u));
   u = __builtin_amdgcn_readfirstlane(u);
-  const uint32_t n = part_slot(a, a.pstride);
-  return buffer_of(reinterpret_cast<const uint8_t*>(a.part) + (size_t)u * n, n);
+  return buffer_of(reinterpret_cast<const uint8_t*>(a.part) +
+                       ((size_t)u * a.pstride + slot) * part_bytes(a),
+                   n * part_bytes(a));
 }
 
 typedef float f2 __attribute__((ext_vector_type(2)));
@@ -1288,7 +1292,7 @@ __device__ __forceinline__ void ld_part(__amdgpu_buffer_rsrc_t p, uint32_t off, 
 }
 
 // Tokens t_lo .. t_hi-1 (at most 32) of the 16-bit residual window of one
-// unit, original domain, to partial `slot`.  One pass from registers: all
+// unit, original domain, to the partial `part`.  One pass from registers: all
 // rows are loaded at once; Q K^T on the matrix cores from the 16-bit rows as
 // they are (exact products, fp32 sums; for a softmax scale far from 1 the
 // bf16 queries times 2^wexp, so that no sum leaves the fp32 range: see
@@ -1302,8 +1306,8 @@ __device__ __forceinline__ void ld_part(__amdgpu_buffer_rsrc_t p, uint32_t off, 
 // tokens by itself.
 template <bool BF16>
 __device__ __forceinline__ void window_chunk_t(const AttnLaunch& a, int b, int h,
-                                               __amdgpu_buffer_rsrc_t part, int slot, int t_lo,
-                                               int t_hi, float* plds) {
+                                               __amdgpu_buffer_rsrc_t part, int t_lo, int t_hi,
+                                               float* plds) {
   static_assert(kResChunk == 32, "two 16-token tiles");
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
   const int col = lane & 15, g = lane >> 4;
@@ -1384,10 +1388,9 @@ __device__ __forceinline__ void window_chunk_t(const AttnLaunch& a, int b, int h
   l += xor_shfl(l, 16);
   l += xor_shfl(l, 32);
   __builtin_amdgcn_wave_barrier();
-  const uint32_t off = part_slot(a, slot);
   if (wave == 0 && lane < a.G) {
     const float ml[2] = {m, l};
-    st_part<2>(part, part_ml(a, off, lane), ml);
+    st_part<2>(part, part_ml(a, lane), ml);
   }
   // P V: channels 32 wave + 2 col, + 1 over tokens 8g .. 8g+7, four queries
   // at a time; then over the four lane rows, row g keeping query 4 jq + g
@@ -1415,7 +1418,7 @@ __device__ __forceinline__ void window_chunk_t(const AttnLaunch& a, int b, int h
 #pragma unroll
     for (int e = 0; e < 2; ++e)
       w[e] = g < 2 ? (g == 0 ? o[0][e] : o[1][e]) : (g == 2 ? o[2][e] : o[3][e]);
-    if (j < a.G) st_part<2>(part, part_acc(off, j, 32 * wave + 2 * col), w);
+    if (j < a.G) st_part<2>(part, part_acc(j, 32 * wave + 2 * col), w);
   }
   if (i_new >= 0 && i_new < n) {
     const size_t dst = (size_t)(a.t_new % cap) * kD;
@@ -1434,10 +1437,10 @@ __device__ __forceinline__ void window_chunk_t(const AttnLaunch& a, int b, int h
 }
 
 __device__ __forceinline__ void window_chunk(const AttnLaunch& a, int b, int h,
-                                             __amdgpu_buffer_rsrc_t part, int slot, int t_lo,
-                                             int t_hi, float* plds) {
-  if (a.is_bf16) window_chunk_t<true>(a, b, h, part, slot, t_lo, t_hi, plds);
-  else window_chunk_t<false>(a, b, h, part, slot, t_lo, t_hi, plds);
+                                             __amdgpu_buffer_rsrc_t part, int t_lo, int t_hi,
+                                             float* plds) {
+  if (a.is_bf16) window_chunk_t<true>(a, b, h, part, t_lo, t_hi, plds);
+  else window_chunk_t<false>(a, b, h, part, t_lo, t_hi, plds);
 }
 
 // Quantized blocks of workgroup slot `slot` of unit (b, h): stream, merge the
@@ -1725,8 +1728,7 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
   }
   __syncthreads();
   // the four waves' results, four channels a thread, to the slot's partial
-  const __amdgpu_buffer_rsrc_t part = part_of(a, unit);
-  const uint32_t off = part_slot(a, slot);
+  const __amdgpu_buffer_rsrc_t part = part_of(a, unit, slot);
   for (int e = tid; e < G * (kD / 4); e += kThreads) {
     const int j = e / (kD / 4), c = 4 * (e % (kD / 4));
     f2 ml[kWaves];
@@ -1747,24 +1749,22 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
       l = __builtin_fmaf(f, ml[w].y, l);
     }
     const float o[4] = {acc[0], acc[1], acc[2], acc[3]}, o2[2] = {M, l};
-    st_part<4>(part, part_acc(off, j, c), o);
-    if (c == 0) st_part<2>(part, part_ml(a, off, j), o2);
+    st_part<4>(part, part_acc(j, c), o);
+    if (c == 0) st_part<2>(part, part_ml(a, j), o2);
   }
 }
 
 // Merge partials of one (batch, kv-head) unit: slots first .. first+count-1
 // (quantized blocks: QuaRot and TurboQuant in the rotated domain) and the
-// nwin window slots win .. win+nwin-1 (original domain).  dst: a partial
-// slot to write the merged (max, sum, acc) to, or -1 to write the unit's
-// output.  Thread t owns E consecutive elements of one query row (128 G / E
+// nwin window slots behind them (original domain).  dst: a partial slot to
+// write the merged (max, sum, acc) to, or -1 to write the unit's output.  Thread t owns E consecutive elements of one query row (128 G / E
 // <= 256); up to kS slots are loaded at once, the
 // missing ones as zeros, so that a merge of up to 16 slots is one latency.
 // Whole workgroup; lds: scratch of 128 G floats, plus the rotation
 // (TurboQuant, 32 KB).
 template <int E>
-__device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit,
-                                           __amdgpu_buffer_rsrc_t part, float* lds, int first,
-                                           int count, int win, int nwin, int dst) {
+__device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit, float* lds,
+                                           int first, int count, int nwin, int dst) {
   constexpr int kS = E <= 4 ? 16 : 8;
   constexpr int TPR = kD / E;              // threads per row
   const int tid = threadIdx.x;
@@ -1791,13 +1791,12 @@ __device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit,
   for (int k = 0; k < E; ++k) num[k] = tail[k] = 0.0f;
   for (int s0 = 0; s0 < ns; s0 += kS) {
     float ml[kS][2], v[kS][E];
+    const __amdgpu_buffer_rsrc_t part = part_of(a, unit, first + s0, ns - s0 < kS ? ns - s0 : kS);
 #pragma unroll
     for (int i = 0; i < kS; ++i) {
-      const int q = s0 + i;
-      const bool any = own && q < ns;
-      const uint32_t so = part_slot(a, q < count ? first + q : win + (q - count));
-      ld_part<2>(part, any ? part_ml(a, so, j) : kNoSlot, ml[i]);
-      ld_part<E>(part, any ? part_acc(so, j, c0) : kNoSlot, v[i]);
+      const uint32_t so = i * part_bytes(a);
+      ld_part<2>(part, own ? so + part_ml(a, j) : kNoSlot, ml[i]);
+      ld_part<E>(part, own ? so + part_acc(j, c0) : kNoSlot, v[i]);
     }
     float mn = M;
 #pragma unroll
@@ -1831,10 +1830,10 @@ __device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit,
   if (dst >= 0) {
     // a group partial (no window in it)
     if (own) {
-      const uint32_t so = part_slot(a, dst);
+      const __amdgpu_buffer_rsrc_t part = part_of(a, unit, dst);
       const float o[2] = {M, den};
-      if (c0 == 0) st_part<2>(part, part_ml(a, so, j), o);
-      st_part<E>(part, part_acc(so, j, c0), num);
+      if (c0 == 0) st_part<2>(part, part_ml(a, j), o);
+      st_part<E>(part, part_acc(j, c0), num);
     }
     return;
   }
@@ -1887,17 +1886,16 @@ __device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit,
   }
 }
 
-__device__ __forceinline__ void merge_slots(const AttnLaunch& a, size_t unit,
-                                            __amdgpu_buffer_rsrc_t part, float* lds, int first,
-                                            int count, int win, int nwin, int dst) {
+__device__ __forceinline__ void merge_slots(const AttnLaunch& a, size_t unit, float* lds,
+                                            int first, int count, int nwin, int dst) {
   if (a.G <= 2)
-    merge_rows<1>(a, unit, part, lds, first, count, win, nwin, dst);
+    merge_rows<1>(a, unit, lds, first, count, nwin, dst);
   else if (a.G <= 4)
-    merge_rows<2>(a, unit, part, lds, first, count, win, nwin, dst);
+    merge_rows<2>(a, unit, lds, first, count, nwin, dst);
   else if (a.G <= 8)
-    merge_rows<4>(a, unit, part, lds, first, count, win, nwin, dst);
+    merge_rows<4>(a, unit, lds, first, count, nwin, dst);
   else
-    merge_rows<8>(a, unit, part, lds, first, count, win, nwin, dst);
+    merge_rows<8>(a, unit, lds, first, count, nwin, dst);
 }
 
 // Arrival tickets on the unit's counters (agent scope); the caller's
@@ -1962,7 +1960,9 @@ attn_kernel(AttnLaunch a) {
   // a unit finishes only after its slowest set-up and its merge, so they
   // go first; the block loops run at normal priority.
   __builtin_amdgcn_s_setprio(kSetupPrio);
-  // The 16-bit window, kResChunk tokens a chunk, chunk c to partial nw + c.
+  const int ng = (nw + kGroup - 1) / kGroup;
+  const int win = nw > kAttnMergeFlat ? nw + ng : nw;   // first window partial
+  // The 16-bit window, kResChunk tokens a chunk, chunk c to partial win + c.
   // With workgroups of its own (win_wg) chunk c belongs to slot nw + c.
   // Else slot s first takes the chunks s, s + nx, .. and then streams its
   // share of the quantized blocks: the window then costs a few workgroups
@@ -1972,7 +1972,7 @@ attn_kernel(AttnLaunch a) {
     const int t_lo = a.nq + c * kResChunk;
     const int t_hi = t_lo + kResChunk < a.n_tokens ? t_lo + kResChunk : a.n_tokens;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    window_chunk(a, b, h, part_of(a, unit), nw + c, t_lo, t_hi,
+    window_chunk(a, b, h, part_of(a, unit, win + c), t_lo, t_hi,
                  reinterpret_cast<float*>(slots + (size_t)wave * a.wave_bytes));
     // the block stream counts this wave's memory operations from zero: the
     // window's partial stores complete first
@@ -1988,10 +1988,9 @@ attn_kernel(AttnLaunch a) {
   // window.  Every counter used is left ready for the next call.
   uint64_t* cnt = a.counters + unit * a.cstride;
   const uint32_t ep = a.epoch;
-  const int ng = (nw + kGroup - 1) / kGroup;
   if (nw <= kAttnMergeFlat) {
     if (take_ticket(cnt, ep) == (uint32_t)(nx - 1)) {
-      merge_slots(a, unit, part_of(a, unit), merge, 0, nw, nw, a.n_rw, -1);
+      merge_slots(a, unit, merge, 0, nw, a.n_rw, -1);
       reset_counter(cnt, ep);
       // every claim group's line (the last arrival: nobody claims now)
       for (int g = 0; g < (ng > 1 ? ng : 1); ++g) reset_counter(cnt + a.claim_off + 16 * g, ep);
@@ -2004,13 +2003,13 @@ attn_kernel(AttnLaunch a) {
     const int gsz = nw - g * kGroup < kGroup ? nw - g * kGroup : kGroup;
     if (take_ticket(cnt + 1 + g, ep) != (uint32_t)(gsz - 1)) return;
     __syncthreads();   // the merge area is read until here
-    merge_slots(a, unit, part_of(a, unit), merge, g * kGroup, gsz, 0, 0, nw + a.n_rw + g);
+    merge_slots(a, unit, merge, g * kGroup, gsz, 0, nw + g);
     reset_counter(cnt + 1 + g, ep);
     // every wave of the group has stopped claiming
     reset_counter(cnt + a.claim_off + 16 * g, ep);
   }
   if (take_ticket(cnt, ep) != (uint32_t)(ng - 1)) return;
-  merge_slots(a, unit, part_of(a, unit), merge, nw + a.n_rw, ng, nw, a.n_rw, -1);
+  merge_slots(a, unit, merge, nw, ng, a.n_rw, -1);
   reset_counter(cnt, ep);
 }
 

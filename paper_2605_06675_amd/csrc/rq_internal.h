@@ -100,9 +100,9 @@ struct AttnLaunch {
   uint16_t* resid_w;      // this layer's window, writable
   int t_new;
   float* part;            // [B][H][pstride] slots of float acc[G][128],
-                          // (max, sum)[G];
-                          // slots 0..n_wg-1 streaming, n_wg..n_wg+n_rw-1
-                          // the residual window, then one per merge group
+                          // (max, sum)[G]; of a unit of kv-head h slots
+                          // 0..nwg[h]-1 streaming, then one per merge group
+                          // (two-level merges), then n_rw for the window
   uint64_t* counters;     // [B][H][cstride] arrival and claim counters:
                           // (epoch << 32) | count
   uint32_t epoch;         // this call's number on the workspace (>= 1)

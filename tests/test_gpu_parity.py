@@ -302,6 +302,37 @@ def test_window_chunks_outnumber_workgroups(T):
     _check_attention(kvc, units, workloads.F16, 2, 2, 4)
 
 
+def test_window_partials_beyond_4gib():
+    """A 16-bit window of 16.6 million tokens at 16 queries a kv-head: its
+    partial results (one of 8320 bytes for 32 tokens) pass 4 GiB.  The keys of
+    the last 16 tokens and of 16 in the middle stand out for one query each;
+    the reference is a plain fp32 softmax."""
+    torch = _torch()
+    G, T = 16, 32 * 518001 + 16
+    assert T // 32 * G * 130 * 4 > 2 ** 32
+    print("window partials beyond 4 GiB", flush=True)
+    if torch.cuda.mem_get_info()[0] < 80 * 2 ** 30:
+        pytest.skip("needs 80 GiB of device memory")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    K, V = (torch.randn((1, 1, T, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+            for _ in range(2))
+    V += 1.0
+    q = torch.randn((1, G, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+    K[0, 0, T // 2:T // 2 + G] = 1.5 * q[0]
+    K[0, 0, T - G:] = 1.5 * q[0]
+    kvc = rq.KVCache(workloads.KIVI, workloads.BF16, 1, 1, 1, G, T + 16, T,
+                     np.array([[[1, 1]]]))
+    kvc.append(0, K, V)
+    out = kvc.attention(0, q)
+    torch.cuda.synchronize()
+    s = (K[0, 0].float() @ q[0].float().T) / math.sqrt(128.0)      # [T][G]
+    p = torch.softmax(s, dim=0)
+    want = p.T @ V[0, 0].float()
+    err = float((out[0] - want).abs().max())
+    print(f"max-abs error {err:.3e}")
+    assert err < ATOL
+
+
 def test_no_window():
     bits = np.array([[[1, 2], [4, 3]]])
     kvc, ks, vs, _ = _build(workloads.KIVI, workloads.BF16, 2, 16, 256, 0,
