@@ -12,7 +12,9 @@
  *  - Plain C types only.  "device" pointers are HIP device memory owned by
  *    the caller; "host" pointers are ordinary host memory owned by the
  *    caller.  The library allocates no device memory and keeps no state
- *    between calls.
+ *    between calls.  k, v, q and the rotations may begin at any element
+ *    (aligned to 16 bytes they are read faster); buffers that the library
+ *    writes are aligned as an allocation is.
  *  - Asynchronous calls enqueue kernels on the given stream and return
  *    without waiting.  Synchronous calls say so.
  *  - Every argument is validated on the host before anything is enqueued;

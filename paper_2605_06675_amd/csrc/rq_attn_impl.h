@@ -856,8 +856,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint3
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)n, 0x00020000);
 }
 
-typedef __attribute__((address_space(3))) void lds_void;
-
 // Cache policy of the block copies: non-temporal (the NT bit), so that the
 // cache blocks streamed once per call are the first to leave the L2 and
 // the kernel's code and small shared data stay there across calls.
@@ -1131,13 +1129,19 @@ __device__ __forceinline__ void dispatch(int bk, int bv, const Geo& g, int depth
 
 // Copy the 16-bit query rows of this kv-head (G x 256 bytes) into qraw with
 // buffer_load_dwordx4 .. lds: wave w moves bytes [1024 w, 1024 w + 1024).
-// Returns the number of copy instructions this wave issued (0 or 1).
+// Returns the number of copy instructions this wave has in flight (0 or 1).
 __device__ __forceinline__ int issue_query(const AttnLaunch& a, int b, int h, int wave,
                                            int lane, uint16_t* qraw) {
   const int bytes = a.G * kD * 2;
   if (1024 * wave >= bytes) return 0;
-  const __amdgpu_buffer_rsrc_t src =
-      buffer_of(a.q + ((size_t)b * a.H * a.G + (size_t)h * a.G) * kD, (uint32_t)bytes);
+  const uint16_t* q = a.q + ((size_t)b * a.H * a.G + (size_t)h * a.G) * kD;
+  if (!lds_copy_aligned(a.q)) {
+    const int i = 64 * wave + lane;
+    if (16 * i < bytes)
+      reinterpret_cast<u4*>(qraw)[i] = gptr(reinterpret_cast<const u4*>(q))[i];
+    return 0;
+  }
+  const __amdgpu_buffer_rsrc_t src = buffer_of(q, (uint32_t)bytes);
   if (1024 * wave + 16 * lane < bytes)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
         src, (lds_void*)(reinterpret_cast<uint8_t*>(qraw) + 1024 * wave), 16,
@@ -1777,14 +1781,19 @@ __device__ __forceinline__ void merge_rows(const AttnLaunch& a, size_t unit, flo
   uint16_t* Rs = reinterpret_cast<uint16_t*>(lds + G * kD);
   if (dst < 0 && a.family == RQ_TURBO) {
     constexpr int kRotBytes = kD * kD * 2;
-    const __amdgpu_buffer_rsrc_t rot =
-        buffer_of(a.rot + (size_t)(unit % a.H) * kD * kD, kRotBytes);
+    const uint16_t* R = a.rot + (size_t)(unit % a.H) * kD * kD;
+    const __amdgpu_buffer_rsrc_t rot = buffer_of(R, kRotBytes);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    if (lds_copy_aligned(a.rot)) {
 #pragma unroll
-    for (int k = 0; k < kRotBytes / (16 * kThreads); ++k)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rot, (lds_void*)(reinterpret_cast<uint8_t*>(Rs) + 16 * kThreads * k + 16 * kWave * wave),
-          16, 16 * kThreads * k + 16 * tid, 0, 0, 0);
+      for (int k = 0; k < kRotBytes / (16 * kThreads); ++k)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rot, (lds_void*)(reinterpret_cast<uint8_t*>(Rs) + 16 * kThreads * k + 16 * kWave * wave),
+            16, 16 * kThreads * k + 16 * tid, 0, 0, 0);
+    } else {
+      for (int i = tid; i < kRotBytes / 16; i += kThreads)
+        reinterpret_cast<u4*>(Rs)[i] = gptr(reinterpret_cast<const u4*>(R))[i];
+    }
   }
   float M = -INFINITY, den = 0.0f, num[E], tail[E];
 #pragma unroll

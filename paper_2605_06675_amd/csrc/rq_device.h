@@ -25,6 +25,15 @@ __device__ __forceinline__ RQ_GLOBAL T* gptr(T* p) {
   return (RQ_GLOBAL T*)p;
 }
 
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Copies from memory straight to LDS move 16 aligned bytes a lane.  Callers'
+// tensors may begin at any element: the others are loaded into registers,
+// whose loads take any address.
+__device__ __forceinline__ bool lds_copy_aligned(const void* p) {
+  return ((uint32_t)(uintptr_t)p & 15u) == 0;
+}
+
 template <bool BF16>
 __device__ __forceinline__ float widen_t(uint32_t bits16) {
   if constexpr (BF16) return __uint_as_float(bits16 << 16);

@@ -57,7 +57,6 @@ __device__ __forceinline__ BlockId block_id(const QuantLaunch& a) {
 }
 
 // ---------------------------------------------------------------- staging
-typedef __attribute__((address_space(3))) void lds_void;
 
 // A block's rows go to LDS as they lie in memory (whole rows per instruction),
 // 16-byte piece s of token t in slot s ^ (t % 8) of the row: the 16 lanes of a
@@ -69,13 +68,15 @@ __device__ __forceinline__ int slot(int t, int piece) {     // dword of the piec
   return t * kRow + 4 * (piece ^ (t & 7));
 }
 
-// The block's rows into LDS, the first 16 tokens by the first four of eight copies.
+// The block's rows into LDS, the first 16 tokens by the first four of eight
+// copies; through registers where some lie in the window or the input is not
+// aligned to the copies' 16 bytes.
 __device__ __forceinline__ void stage_rows(const QuantLaunch& a, int b, int h, int kind, int t0,
                                            int lane, uint32_t* sm) {
   const uint16_t* in = (kind ? a.v : a.k) + (size_t)(b * a.H + h) * a.n_new * kD;
   const int g = lane >> 4;
   const int piece[2] = {(lane & 15) ^ g, (lane & 15) ^ g ^ 4};   // of token 4 j + g
-  if (t0 >= a.n_past) {                                  // the same for the wave
+  if (t0 >= a.n_past && lds_copy_aligned(in)) {          // the same for the wave
     const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t*>(in + (size_t)(t0 - a.n_past) * kD), 0, kChunk * kD * 2, 0x00020000);
     if (a.stream) {

@@ -519,6 +519,51 @@ def test_chunked_window_copies(family, R):
     _check_cache(family, dtype, kvc, ks, vs, bits, R, B, H, T)
 
 
+@pytest.mark.parametrize("offset", [1, 2, 4])
+@pytest.mark.parametrize("family", [workloads.KIVI, workloads.QUAROT, workloads.RTN,
+                                    workloads.KIVI_RTN, workloads.TURBO])
+def test_inputs_at_any_element(family, offset):
+    """K, V, queries and rotations that begin 2, 4 or 8 bytes behind a 16-byte boundary
+    (contiguous views into a larger buffer) give what aligned ones do, bit for
+    bit: one long append, one over the window's edge, decode steps."""
+    torch = _torch()
+    B, H, G, R, T, dtype = 2, 3, 4, 32, 300, workloads.BF16
+    bits = np.array([[[3, 4], [2, 5], [4, 2]]], dtype=np.uint8)
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def placed(x, off):
+        buf = torch.empty(x.numel() + 8, dtype=x.dtype, device="cuda")
+        view = buf[off:off + x.numel()].view(x.shape)
+        view.copy_(x)
+        assert view.data_ptr() % 16 == 2 * off and view.is_contiguous()
+        return view
+
+    K, V = (torch.randn((B, H, T, 128), generator=g, device="cuda").to(torch.bfloat16)
+            for _ in range(2))
+    q = torch.randn((B, H * G, 128), generator=g, device="cuda").to(torch.bfloat16)
+    rot = torch.linalg.qr(torch.randn((1, H, 128, 128), generator=torch.Generator().manual_seed(5)))
+    rot = rot.Q.to(torch.bfloat16).cuda() if family == workloads.TURBO else None
+    got = []
+    for off in (0, offset):
+        kvc = rq.KVCache(family, dtype, 1, B, H, H * G, 320, R, bits,
+                         rotation=None if rot is None else placed(rot, off))
+        t0, outs = 0, []
+        for n in (200, 80):
+            kvc.append(0, *(placed(x[:, :, t0:t0 + n].contiguous(), off) for x in (K, V)))
+            t0 += n
+            outs.append(kvc.attention(0, placed(q, off)).clone())
+        for t in range(t0, T):
+            outs.append(kvc.decode_step(
+                0, *(placed(x[:, :, t:t + 1].contiguous(), off) for x in (K, V)),
+                placed(q, off)).clone())
+        torch.cuda.synchronize()
+        got.append((gh.read_buffers(kvc), [o.cpu().numpy() for o in outs]))
+    for a, b in zip(got[0][0], got[1][0]):
+        np.testing.assert_array_equal(a, b)
+    for a, b in zip(got[0][1], got[1][1]):
+        np.testing.assert_array_equal(a, b)
+
+
 def test_kivi_orders_of_workgroups():
     """Units of 191 and 192 blocks (the line between the two orders) in one
     launch against the same tokens in launches of fewer blocks."""
