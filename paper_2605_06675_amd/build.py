@@ -56,6 +56,7 @@ def _compile(src):
             raise RuntimeError(f"{src}: device code contains a function call")
         if src.startswith("rq_attn"):
             _check_claim_registers(src, text)
+            _check_block_loops(src, text)
     return obj
 
 
@@ -81,6 +82,31 @@ def _check_claim_registers(src, text):
                 if _CLAIM_REGS & set(range(lo, hi + 1)):
                     raise RuntimeError(f"{src}: compiler-generated use of a "
                                        f"claim register: {t}")
+
+
+_LABEL = re.compile(r"(\.LBB\d+_\d+|; %bb\.\d+):")
+_LDS_COPY = re.compile(r"\tbuffer_load_dwordx4\b.*\blds\b")
+
+
+def _check_block_loops(src, text):
+    """What the block loops of the attention kernels must not hold: a scratch
+    access (its wait is one for every block copy in flight), and a loop around
+    a block copy that reads its buffer resource out of vector registers (a
+    resource the compiler does not know to be uniform: several v_readfirstlane
+    a copy, where a kernel otherwise has a few hundred for all of its copies)."""
+    in_loop = False
+    for line in text.split("\n"):
+        t = line.strip()
+        if _LABEL.match(line):
+            in_loop = "Loop" in line
+        elif t.startswith(";"):
+            in_loop = in_loop or "Loop" in t
+        elif in_loop and t.startswith(("scratch_load", "scratch_store")):
+            raise RuntimeError(f"{src}: scratch access in a loop: {t}")
+    copies = len(_LDS_COPY.findall(text))
+    if text.count("\tv_readfirstlane") >= max(copies, 1):
+        raise RuntimeError(f"{src}: {copies} block copies, {text.count('v_readfirstlane')} "
+                           "v_readfirstlane: resources in vector registers")
 
 
 def build(verbose=False):

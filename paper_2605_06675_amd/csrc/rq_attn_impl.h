@@ -856,6 +856,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint3
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)n, 0x00020000);
 }
 
+// p (the same in every lane) in scalar registers
+__device__ __forceinline__ const uint8_t* scalar_ptr(const uint8_t* p) {
+  const uint64_t u = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  return (const uint8_t*)(((uint64_t)hi << 32) | lo);
+}
+
 // Cache policy of the block copies: non-temporal (the NT bit), so that the
 // cache blocks streamed once per call are the first to leave the L2 and
 // the kernel's code and small shared data stay there across calls.
@@ -1468,10 +1476,10 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
     const size_t v0 = a.tab.code_off[h][1] + (size_t)b * a.cap * 16 * bv;
     const size_t km0 = meta_unit_offset(FAM, h, 0, b, a.B, nblk_cap);
     const size_t vm0 = meta_unit_offset(FAM, h, 1, b, a.B, nblk_cap);
-    g.voff = (uint32_t)(v0 - k0);
-    g.vmoff = (uint32_t)(vm0 - km0);
-    g.codes = buffer_of(a.codes + k0, g.voff + (uint32_t)a.cap * 16 * bv);
-    g.meta = buffer_of(a.meta + km0, g.vmoff + (uint32_t)nblk_cap * mv);
+    g.voff = __builtin_amdgcn_readfirstlane((uint32_t)(v0 - k0));
+    g.vmoff = __builtin_amdgcn_readfirstlane((uint32_t)(vm0 - km0));
+    g.codes = buffer_of(scalar_ptr(a.codes + k0), g.voff + (uint32_t)a.cap * 16 * bv);
+    g.meta = buffer_of(scalar_ptr(a.meta + km0), g.vmoff + (uint32_t)nblk_cap * mv);
   }
   const int nblk = a.nq / kChunk;
   // this unit's ring: as many whole blocks as the wave's region holds

@@ -305,3 +305,19 @@ def test_sensitivity_validates_before_launch():
                             1 << 20, None) == rq.RQ_EINVAL      # misaligned
     assert L.rq_sensitivity(rq.RQ_F32, fake, 1, 4, 8, wp, fake, 8,
                             None) == rq.RQ_ESMALLWS
+
+
+def test_build_rejects_slow_block_loops():
+    """The checks of the attention kernels' assembly: scratch accesses inside a
+    loop and buffer resources read out of vector registers copy by copy."""
+    from paper_2605_06675_amd import build
+    copy = "\tbuffer_load_dwordx4 v1, s[0:3], 0 offen lds\n"
+    loop = ".LBB0_1:          ; =>This Inner Loop Header: Depth=1\n"
+    spill = "\tscratch_load_dword v1, off, off\n"
+    build._check_block_loops("f", spill + loop + copy + "; %bb.2:\n" + spill)
+    with pytest.raises(RuntimeError, match="scratch"):
+        build._check_block_loops("f", loop + copy + spill)
+    with pytest.raises(RuntimeError, match="scratch"):
+        build._check_block_loops("f", ".LBB0_1:\n  ;   in Loop: Header=BB0_1 Depth=1\n" + copy + spill)
+    with pytest.raises(RuntimeError, match="resources"):
+        build._check_block_loops("f", loop + "\tv_readfirstlane_b32 s0, v0\n" * 4 + copy)
