@@ -202,7 +202,8 @@ __device__ __forceinline__ uint32_t norm_of(const u4* x) {
 // turned into codes together (codes_of_fields).  The sign is t's sign bit,
 // and t = 0 (a zero coordinate, a token of norm zero) belongs to the
 // negative side: t is formed by a fused multiply-add of -2^-149, fp32's
-// least subnormal, which leaves every other rounded product as it is.
+// least subnormal, which leaves every other rounded product as it is (a product
+// halfway between two fp32 values may round the other way).
 //
 // Widths 1..3: the bits of a field are compared one by one (bisection over
 // th) and shifted into the quarter's dword, one add with carry per bit, so
@@ -224,8 +225,9 @@ struct Cell {
 };
 
 __device__ __forceinline__ uint32_t cell_of(float ts, int cells) {
-  const uint32_t c = (uint32_t)__builtin_fabsf(ts);
-  return c < (uint32_t)cells ? c : (uint32_t)cells - 1u;
+  // (clamped as a float: a token of saturated norm reaches values whose
+  // conversion is not defined; a NaN takes cell 0)
+  return (uint32_t)__builtin_amdgcn_fmed3f(__builtin_fabsf(ts), 0.0f, (float)(cells - 1));
 }
 
 // Tables of the head's K (kind 0) and V widths; whole workgroup.

@@ -159,6 +159,23 @@ def test_turbo_norms_at_fp16_midpoints(dtype):
     _check(dtype, kvc, [kv[0]], [kv[1]], rf[0], bits, 0, 1, H)
 
 
+@pytest.mark.parametrize("scale", [1e5, 1e12, 1e30])
+def test_turbo_saturated_norms(scale):
+    # tokens whose norm saturates at 65504: coordinates over it grow beyond
+    # every threshold, past 2^32 and far past, and take the outermost codes
+    H, T = 4, 64
+    bits = np.array([[[1, 8], [4, 2], [5, 6], [7, 3]]])
+    rng = np.random.default_rng(6)
+    r16, rf = _rotations(1, H)
+    kv = workloads.bits16_from_f32(
+        (rng.standard_normal((2, H, T, 128)) * scale).astype(np.float32), workloads.BF16)
+    kvc = rq.KVCache(rq.RQ_TURBO, workloads.BF16, 1, 1, H, H, T, 0, bits,
+                     rotation=gh.dev(r16, workloads.BF16))
+    kvc.append(0, *(gh.dev(kv[i][None], workloads.BF16) for i in range(2)))
+    _torch().cuda.synchronize()
+    _check(workloads.BF16, kvc, [kv[0]], [kv[1]], rf[0], bits, 0, 1, H)
+
+
 def test_turbo_quantize_wide_widths_chunked():
     bits = np.array([[[5, 6], [7, 8]]])
     kvc, ks, vs, Rf = _build(workloads.BF16, 2, 230, 40, bits, 1,
