@@ -510,10 +510,16 @@ rq_status rq_quantize_kv(const rq_cache* c, int32_t layer, int32_t n_past,
   // a row it writes could take the ring slot of a token a flushed block still
   // reads there (tokens [nq_old, min(nq_new, n_past)) are read from the
   // ring); then the wave that reads it where that is one wave a unit and kind
-  // (windows of one block: chunked prefill), else a launch of its own
-  // (TurboQuant's waves share their rows).  RTN, 3001 tokens of 8 kv-heads in
-  // chunks of 512, window of 32: 10.4 us a chunk with two launches, 8.1 with
-  // one; KIVI, 11 x 8 x 23831 in chunks of 2048: 26.8 and 24.5 us.
+  // (a window of one block, or one that the old tokens only begin to fill)
+  // and it has few rows to copy, else a launch of its own (TurboQuant's waves
+  // share their rows).  RTN, 3001 tokens of 8 kv-heads in chunks of 512,
+  // window of 32: 10.4 us a chunk with two launches, 8.1 with one; KIVI, 11 x
+  // 8 x 23831 in chunks of 2048: 26.8 and 24.5 us.  A long append to 20
+  // tokens, KIVI, one launch / two, us, by waves and rows: 16 waves 63 rows
+  // 6.1 / 6.2, 95 rows 6.8 / 6.2, 1055 rows 28 / 10; 32 waves 95 rows 7.2 / 7.1,
+  // 159 rows 8.5 / 7.6; 64 waves 159 rows 8.7 / 8.8, 287 rows 11.5 / 10.8; 96
+  // waves 287 rows 11.8 / 13.0, 1055 rows 34 / 29; 128 waves 1055 rows 34 / 36;
+  // 256 waves 4127 rows 193 / 233.
   const int nq_old = n_quantized(n_past, c->residual);
   const int read_hi = nq_new < n_past ? nq_new : n_past;
   const bool reads_ring = nq_old < read_hi;
@@ -521,8 +527,10 @@ rq_status rq_quantize_kv(const rq_cache* c, int32_t layer, int32_t n_past,
   if (q.nblk > 0) {
     if (!reads_ring || T_new - 1 - nq_old < c->residual + rq::kChunk)
       q.ring_fused = rq::kRingAny;
-    else if (read_hi - nq_old <= rq::kChunk && c->family != RQ_TURBO)
-      q.ring_fused = rq::kRingFirst;
+    else if (read_hi - nq_old <= rq::kChunk && c->family != RQ_TURBO) {
+      const int64_t waves = (int64_t)2 * c->batch * c->n_kv_heads, rows = r.t_hi - r.t_lo;
+      if (waves >= 128 || rows < 64 || rows < 4 * waves) q.ring_fused = rq::kRingFirst;
+    }
   }
   hipError_t e = rq::launch_quantize(q, s);
   if (e != hipSuccess) return hip_fail(e, "quantize launch");

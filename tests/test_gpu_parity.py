@@ -519,6 +519,18 @@ def test_chunked_window_copies(family, R):
     _check_cache(family, dtype, kvc, ks, vs, bits, R, B, H, T)
 
 
+@pytest.mark.parametrize("B,H,R", [(1, 4, 32), (1, 4, 64), (1, 8, 96), (8, 8, 96)])
+@pytest.mark.parametrize("family", [workloads.KIVI, workloads.RTN])
+def test_long_append_to_a_few_tokens(family, B, H, R):
+    """A window that 20 tokens begin to fill and one append fills and passes:
+    its rows copied by the waves of the first blocks (few rows, or many such
+    waves) or by a launch of their own."""
+    dtype, T = workloads.BF16, 20 + R + 64 + 11
+    bits = np.array([[[2 + h % 2, 3] for h in range(H)]], dtype=np.uint8)
+    kvc, ks, vs, _ = _build(family, dtype, H, 2, T, R, bits, batch=B, chunks=[20, T - 20])
+    _check_cache(family, dtype, kvc, ks, vs, bits, R, B, H, T)
+
+
 @pytest.mark.parametrize("offset", [1, 2, 4])
 @pytest.mark.parametrize("family", [workloads.KIVI, workloads.QUAROT, workloads.RTN,
                                     workloads.KIVI_RTN, workloads.TURBO])
