@@ -1,4 +1,5 @@
 // C-ABI entry points: validation, cache layout, launch set-up.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -163,42 +164,6 @@ struct SplitPlan {
   int pstride;                       // partial slots per unit
 };
 
-// LDS shape of the attention kernel for one layer: the most workgroups per
-// CU (three, the kernel's occupancy, down to one) whose share of the CU's
-// LDS gives every wave a ring of at least two blocks of the layer's widest
-// kv-head.  A share is rounded down to whole 2 KiB (an allocation granule
-// coarser than 512 bytes was measured to lose the third workgroup), less
-// 64 bytes for the static LDS.  False when not even one workgroup per CU
-// fits.
-struct AttnShape {
-  int wg_per_cu, wave_bytes;
-  size_t lds;
-};
-
-//
-// TurboQuant layers of widths up to 4 start from two: their workgroups begin
-// with the rotation of the queries and are bound by LDS reads, which two
-// rings of more blocks serve as well as three, so fewer set-ups and partials
-// gain (4 x 8 units of 32768 tokens at 3 bits 56.7 -> 54.5 us, 4 of 24941 at
-// 3.5 bits 28.1 -> 26.1; with widths to 6, 8 units of 97088 lose: 50.2 ->
-// 52.6; KIVI 16 x 8 units of 8192 33.4 -> 36.2).
-bool attn_shape(const rq_cache* c, int max_blk_bytes, int max_bits, AttnShape* out) {
-  const int G = c->n_q_heads / c->n_kv_heads;
-  const size_t tail = rq::attention_tail_bytes(G, c->family);
-  for (int w = c->family == RQ_TURBO && max_bits <= 4 ? 2 : 3; w >= 1; --w) {
-    size_t share = (lds_per_cu() / w) / 2048 * 2048 - 64;
-    share = share < lds_limit() ? share : lds_limit();
-    if (share <= tail) continue;
-    const int wave = (int)((share - tail) / rq::kAttnWaves / 16 * 16);
-    if (wave < 2 * max_blk_bytes) continue;
-    const size_t lds = rq::attention_lds_bytes(G, wave, c->family);
-    if (lds > share) continue;
-    *out = AttnShape{w, wave, lds};
-    return true;
-  }
-  return false;
-}
-
 // Compute units of the current device (queried once; 256 when no device
 // can be queried, e.g. for host-only sizing calls).
 int cu_count() {
@@ -214,6 +179,62 @@ int cu_count() {
       n = 256;
   }
   return n;
+}
+
+// LDS shape of the attention kernel for one layer: the most workgroups per
+// CU (three, the kernel's occupancy, down to one) whose share of the CU's
+// LDS gives every wave a ring of at least two blocks of the layer's widest
+// kv-head.  A share is rounded down to whole 2 KiB (an allocation granule
+// coarser than 512 bytes was measured to lose the third workgroup), less
+// 64 bytes for the static LDS.  two: at most two.  False when not even one
+// workgroup per CU fits.
+struct AttnShape {
+  int wg_per_cu, wave_bytes;
+  size_t lds;
+};
+
+// TurboQuant layers of widths up to 4 take two a CU where that is faster:
+// their workgroups begin with the rotation of the queries, so where the blocks
+// are few, fewer set-ups and partials gain, also in throughput as long as the
+// units fill two workgroups a CU to the last one (powers of two) and are few.
+// us with two / three a CU, widths 2..4, by units x tokens: 4 queries a
+// kv-head 80 x 2048 22.7 / 23.6, 128 x 2048 25.3 / 25.9, 40 x 8192 28.5 / 29.1, 64 x
+// 8192 32.5 / 32.3, 96 x 8192 42.1 / 37.2, 192 x 8192 82.2 / 61.1, 16 x 32768
+// 37.3 / 38.2, 24 x 32768 43.8 / 40.3, 32 x 32768 52.7 / 53.1, 40 x 32768 60.1
+// / 56.6, 64 x 32768 78.0 / 71.2; 8 queries 128 x 2048 28.3 / 31.0, 40 x 8192
+// 31.6 / 33.3, 32 x 32768 55.8 / 57.6, 64 x 32768 81.1 / 75.6.  Three a CU
+// that merge in two levels are slower too (4 queries, 20 x 8192 23.8 / 25.9,
+// 23 x 32768 44.3 / 44.5).  One or two queries have little to set up and gain
+// only in those merges, where two fill the CUs (4 x 32768 20.0 / 22.2, 16 x
+// 8192 20.6 / 23.3, but 12 x 32768 28.4 / 27.2, 20 x 32768 36.6 / 34.6, 40 x
+// 8192 26.0 / 25.5, 96 x 2048 22.6 / 20.4).
+// Wider layers and the other families lose (TurboQuant to 6 bits, 8 units of
+// 97088 tokens 52.6 / 50.2; KIVI, 128 units of 8192 36.2 / 33.4).
+bool two_per_cu(const rq_cache* c, int max_bits, int n_tokens) {
+  if (c->family != RQ_TURBO || max_bits > 4) return false;
+  const long units = (long)c->batch * c->n_kv_heads, cus = cu_count();
+  const long nblk = n_quantized(n_tokens, c->residual) / rq::kChunk, most = (nblk + 3) / 4;
+  const bool fills = 2 * cus % units == 0, few = c->n_q_heads <= 2 * c->n_kv_heads;
+  if (std::min(3 * cus / units, most) > rq::kAttnMergeFlat) return fills || !few;
+  if (few) return false;
+  return (units <= 32 && fills) || (units <= 128 && units * nblk <= 10240);
+}
+
+bool attn_shape(const rq_cache* c, int max_blk_bytes, bool two, AttnShape* out) {
+  const int G = c->n_q_heads / c->n_kv_heads;
+  const size_t tail = rq::attention_tail_bytes(G, c->family);
+  for (int w = two ? 2 : 3; w >= 1; --w) {
+    size_t share = (lds_per_cu() / w) / 2048 * 2048 - 64;
+    share = share < lds_limit() ? share : lds_limit();
+    if (share <= tail) continue;
+    const int wave = (int)((share - tail) / rq::kAttnWaves / 16 * 16);
+    if (wave < 2 * max_blk_bytes) continue;
+    const size_t lds = rq::attention_lds_bytes(G, wave, c->family);
+    if (lds > share) continue;
+    *out = AttnShape{w, wave, lds};
+    return true;
+  }
+  return false;
 }
 
 // Merge groups of a unit's workgroups (the two-level merge starts above
@@ -347,7 +368,7 @@ rq_status decode_attention(const rq_cache* c, int32_t layer, int32_t n_tokens, c
     }
   }
   AttnShape shape;
-  if (!attn_shape(c, max_blk, max_bits, &shape))
+  if (!attn_shape(c, max_blk, two_per_cu(c, max_bits, n_tokens), &shape))
     return fail(RQ_EUNSUPPORTED,
                 "layer %d: two %d-byte blocks per wave do not fit the LDS of a CU "
                 "(K+V bit-widths of one kv-head are too wide)", layer, max_blk);

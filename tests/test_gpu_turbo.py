@@ -293,6 +293,16 @@ def test_turbo_calibration_sweep(dtype, bits):
     np.testing.assert_allclose(b, wb, rtol=1e-4)
 
 
+@pytest.mark.parametrize("batch,G", [(17, 4), (16, 4), (2, 1)])
+def test_turbo_attention_workgroups_per_cu(batch, G):
+    # 136 units and a single query a kv-head take three workgroups a CU, 128
+    # units two (rings of other depths, other splits of the blocks)
+    bits = np.array([[[2 + h % 3, 4 - h % 3] for h in range(8)]])
+    kvc, ks, vs, Rf = _build(workloads.BF16, 8, 540, 32, bits, batch, G=G)
+    units = _check(workloads.BF16, kvc, ks, vs, Rf, bits, 32, batch, 8)
+    _attention(kvc, units, workloads.BF16, batch, 8, G)
+
+
 def test_turbo_attention_two_level_merge():
     # batch 1, two kv-heads, 4096 tokens: partials merged in groups first
     bits = np.array([[[3, 2], [4, 3]]])
