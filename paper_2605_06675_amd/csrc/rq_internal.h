@@ -28,9 +28,12 @@ __host__ __device__ inline size_t meta_unit_offset(int family, int h, int kind, 
          (size_t)b * nblk_cap * (kind ? mv : mk);
 }
 constexpr int kAttnGroup = 16;        // streaming slots per merge group
-// At most this many slots: one merge level (24 slots in two rounds of loads
-// take less than a second ticket and merge: 57.6 -> 56.7 us at 4 x 8 units of
-// 24 TurboQuant slots).
+// At most this many slots: one merge level (two rounds of loads, four for more
+// than eight queries, take less than a second ticket and merge).  us with one
+// / two levels, units of 16384 tokens: KIVI, 4 queries a kv-head, 18 slots 28.7 /
+// 30.4, 24 slots 26.8 / 28.5, 32 slots 24.3 / 25.1; 16 queries 31.9 / 31.9, 29.2 /
+// 30.3, 28.1 / 28.9; TurboQuant, 8 queries, 24 slots 35.1 / 36.7, 32 slots 32.4 / 32.5;
+// the one loss seen: KIVI_RTN, 16 queries, 32 slots 29.7 / 28.7.
 constexpr int kAttnMergeFlat = 32;
 constexpr int kAttnResChunk = 32;     // window tokens per window workgroup
 constexpr int kAttnMaxDepth = 4;      // most blocks in flight per attention wave

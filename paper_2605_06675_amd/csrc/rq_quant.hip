@@ -744,7 +744,12 @@ constexpr size_t kStreamBytes = (size_t)96 << 20;
 // time): KIVI 2.5 bits, 8 kv-heads, by batch / by head, us: 16 x 2048 tokens
 // 31.2 / 32.9, 64 x 2048 114.1 / 122.5, 16 x 4096 58.8 / 58.5, 32 x 4096
 // 113.3 / 114.0, 11 x 8192 80.7 / 78.8, 16 x 8192 115.5 / 107.9, 16 x 16384
-// 225.9 / 212.7.
+// 225.9 / 212.7.  The other kernels: 64 x 2048 RTN 4 bits 110 / 128, QuaRot
+// 116 / 128, KIVI_RTN 114 / 124; 16 x 8192 RTN 4 bits 127 / 114, 3 bits 107 /
+// 108, QuaRot 4 bits 130 / 114, 2..6 bits 119 / 121, KIVI 4 bits 133 / 116, 2..6
+// bits 124 / 123, KIVI_RTN 112 / 116 (by batch, power-of-two strides of 4-bit
+// codes collide); 8 x 16384 in that order 123 / 105, 106 / 101, 135 / 108, 119 /
+// 115, 131 / 110, 123 / 118, 111 / 106.
 dim3 set_grid(QuantLaunch& q) {
   q.stream = (size_t)q.nblk * q.H * q.B * q.kind_n * (kChunk * kD * 2) > kStreamBytes;
   q.by_batch = q.nblk < 192 && q.B <= 65535;      // (the grid's limit along z)
