@@ -2,8 +2,13 @@
 the library's cache buffers back according to the documented layout (the
 offsets are recomputed here from the layout formula, not asked of the
 library)."""
+import collections
+import os
+import re
+
 import numpy as np
 
+import paper_2605_06675_amd as rq
 import workloads
 from oracle import cache as ocache
 
@@ -88,6 +93,42 @@ def compare_unit(lay, bufs, l, b, h, unit, k16, v16):
         for t in range(nq, T):
             np.testing.assert_array_equal(ring[ocache.ring_slot(t, lay.R)],
                                           src[t])
+
+
+Plan = collections.namedtuple("Plan", "workgroups chunks own_chunks groups")
+
+
+def split_plan(desc, n_tokens, per_cu=3):
+    """How an attention call over n_tokens splits a unit: its streaming
+    workgroups, its window chunks of 32 tokens, whether these have workgroups
+    of their own, and the groups of a two-level merge (0: one level).
+    per_cu: workgroups a CU (TurboQuant of widths up to 4: 2 or 3).  The
+    library's line between the levels is read from its source, and what it
+    reports as workspace must be what this plan needs at three a CU."""
+    import torch
+    with open(os.path.join(rq.HERE, "csrc", "rq_internal.h")) as f:
+        src = f.read()
+    flat, group = (int(re.search(rf"constexpr int {n} = (\d+);", src).group(1))
+                   for n in ("kAttnMergeFlat", "kAttnGroup"))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    units = desc.batch * desc.n_kv_heads
+    nq = max(0, (n_tokens - desc.residual) // 32 * 32)
+    chunks = -(-(n_tokens - nq) // 32)
+
+    def plan(per_cu):
+        budget = cus * per_cu // units
+        nw = min(max(budget, 1), (nq // 32 + 3) // 4) if nq else 0
+        own = chunks > 0 and (nw == 0 or nw + chunks <= budget) and nw + chunks <= flat
+        return Plan(nw, chunks, own, -(-nw // group) if nw > flat else 0)
+
+    most = -(-((desc.capacity // 32 + 3) // 4) // group)
+    stride = 16 * ((1 + most + 15) // 16) + 16 * most
+    p = plan(3)
+    slots = max(1, p.workgroups + p.chunks + p.groups)
+    assert rq.rq_decode_workspace(desc, n_tokens) == (
+        -(-units * stride * 8 // 256) * 256
+        + units * slots * (desc.n_q_heads // desc.n_kv_heads) * 130 * 4)
+    return plan(per_cu)
 
 
 def read_buffers(kvc):

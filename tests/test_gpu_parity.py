@@ -193,8 +193,8 @@ def test_kivi_decode_steps_with_flushes():
 
 @pytest.mark.parametrize("G", [4, 8])
 def test_kivi_two_level_merge_long_context(G):
-    """Two kv-heads, batch 1, 8000+ tokens: more than 16 workgroups per
-    unit, so partials are merged in groups first.  Attention after the
+    """Two kv-heads, batch 1, 8000+ tokens: more workgroups per unit than
+    one merge takes, so partials are merged in groups first.  Attention after the
     prefill and after appends that change the number of workgroups (the
     counters must be ready for the next call every time)."""
     torch = _torch()
@@ -213,6 +213,7 @@ def test_kivi_two_level_merge_long_context(G):
     for n in (T0, 1, 150, 149):
         kvc.append(0, K[:, :, t:t + n].contiguous(), V[:, :, t:t + n].contiguous())
         t += n
+        assert gh.split_plan(kvc.desc, t).groups >= 4
         out = kvc.attention(0, qd).cpu().numpy()
         for h in range(H):
             u = ocache.Unit(workloads.KIVI,
@@ -225,6 +226,25 @@ def test_kivi_two_level_merge_long_context(G):
     torch.cuda.synchronize()
     print(f"long-context attention max-abs error {worst:.3e}")
     assert worst < ATOL
+
+
+@pytest.mark.parametrize("family,G,widest", [
+    (workloads.KIVI, 1, 6), (workloads.KIVI, 16, 4), (workloads.QUAROT, 4, 4),
+    (workloads.QUAROT, 16, 6), (workloads.RTN, 8, 4), (workloads.KIVI_RTN, 4, 6),
+    (workloads.KIVI_RTN, 16, 4)])
+def test_two_level_merge(family, G, widest):
+    """More workgroups a unit than one merge takes, in every family (QuaRot
+    rotates the output of the second level), with a window of several chunks;
+    two calls, the second on the counters that the first one left."""
+    H, T, R = 2, 4700, 80
+    bits = np.array([[[2, widest], [widest, 3]]])
+    print(f"two-level merge family {family} G {G}", flush=True)
+    kvc, ks, vs, _ = _build(family, workloads.BF16, H, G, T, R, bits)
+    plan = gh.split_plan(kvc.desc, T)
+    assert plan.groups == 3 and plan.chunks >= 3
+    units = _check_cache(family, workloads.BF16, kvc, ks, vs, bits, R, 1, H, T)
+    for call in range(2):
+        _check_attention(kvc, units, workloads.BF16, 1, H, G, seed=7 + call)
 
 
 @pytest.mark.parametrize("family,G", [(workloads.KIVI, 1), (workloads.KIVI, 3),
@@ -250,15 +270,16 @@ def test_stale_workspace_counters(fill):
     """A workspace whose counters hold counts of other calls (foreign tags,
     arbitrary counts: what a call that did not finish leaves) or random
     bytes: the call replaces the stale counts and matches the oracle, and
-    the call after it (on counters this call readied) does too.  4100
+    the call after it (on counters this call readied) does too.  4500
     tokens over 2 x 4 units: two-level merges with claims in each group."""
     torch = _torch()
-    H, G, T = 4, 4, 4100
+    H, G, T = 4, 4, 4500
     bits = np.array([[[2, 3], [1, 4], [3, 2], [4, 1]]])
     kvc, ks, vs, _ = _build(workloads.KIVI, workloads.BF16, H, G, T, 32, bits,
                             batch=2)
     units = _check_cache(workloads.KIVI, workloads.BF16, kvc, ks, vs, bits, 32,
                          2, H, T)
+    assert gh.split_plan(kvc.desc, T).groups == 3
     ws = kvc.workspace(T)
     rng = np.random.default_rng(17)
     n8 = ws.numel() // 8
@@ -291,15 +312,66 @@ def test_short_context_window_only():
 @pytest.mark.parametrize("T", [100, 200, 700])
 def test_window_chunks_outnumber_workgroups(T):
     # a 160-token window is 5 or 6 chunks of 32 tokens, more than the few
-    # streaming workgroups of these short caches, so a workgroup takes
-    # several chunks before its blocks (T=100: nothing quantized, one
-    # workgroup takes every chunk; T=700: 5 workgroups, 6 chunks)
+    # streaming workgroups of these short caches; the chip has room for a
+    # workgroup a chunk (T=100: nothing quantized; T=700: 5 workgroups, 6
+    # chunks)
     bits = np.array([[[2, 3], [4, 1]]])
     kvc, ks, vs, _ = _build(workloads.KIVI, workloads.F16, 2, 4, T, 160,
                             bits, batch=2, cap=768)
     units = _check_cache(workloads.KIVI, workloads.F16, kvc, ks, vs, bits,
                          160, 2, 2, T)
+    plan = gh.split_plan(kvc.desc, T)
+    assert plan.own_chunks and plan.chunks > plan.workgroups
     _check_attention(kvc, units, workloads.F16, 2, 2, 4)
+
+
+@pytest.mark.parametrize("family", [workloads.KIVI, workloads.QUAROT, workloads.RTN,
+                                    workloads.TURBO, workloads.KIVI_RTN])
+def test_window_chunks_before_blocks(family):
+    """800 units, more than the chip holds workgroups: a unit's only workgroup
+    takes all chunks of the window and then streams the blocks through the same
+    LDS.  Attention after the prefill, and decode steps up to and across two
+    flushes, whose new token lies in the last of four to six chunks; sampled
+    units against the oracle."""
+    torch = _torch()
+    from tests import test_gpu_turbo as gt
+    B, H, G, R, T0, dtype = 100, 8, 4, 128, 436, workloads.F16
+    steps = 48
+    T = T0 + steps
+    bits = np.array([[[2 + h % 3, 4 - h % 3] for h in range(H)]])
+    g = torch.Generator(device="cuda").manual_seed(9)
+    K, V = (torch.randn((B, H, T, 128), generator=g, device="cuda").to(torch.float16)
+            for _ in range(2))
+    rot = rf = None
+    if family == workloads.TURBO:
+        r16, rf = gt._rotations(1, H)
+        rot = gh.dev(r16, workloads.BF16)
+    kvc = rq.KVCache(family, dtype, 1, B, H, H * G, 512, R, bits, rotation=rot)
+    print(f"window chunks before blocks, family {family}", flush=True)
+    kvc.append(0, K[:, :, :T0].contiguous(), V[:, :, :T0].contiguous())
+    seen = set()
+    for t in range(T0, T + 1):
+        q = torch.randn((B, H * G, 128), generator=g, device="cuda").to(torch.float16)
+        if t == T0:
+            out = kvc.attention(0, q)
+        else:
+            out = kvc.decode_step(0, K[:, :, t - 1:t].contiguous(),
+                                  V[:, :, t - 1:t].contiguous(), q)
+        plan = gh.split_plan(kvc.desc, t)
+        assert plan.workgroups == 1 and not plan.own_chunks and plan.chunks >= 4
+        seen.add(plan.chunks)
+        if t not in (T0, T0 + 1, 447, 448, 449, 479, 480, 481, T):
+            continue
+        torch.cuda.synchronize()
+        for b, h in ((0, 0), (57, 3), (99, 7)):
+            u = ocache.Unit(family, K[b, h, :t].float().cpu().numpy(),
+                            V[b, h, :t].float().cpu().numpy(), int(bits[0, h, 0]),
+                            int(bits[0, h, 1]), R, rotation=None if rf is None else rf[0][h])
+            qh = q[b, h * G:(h + 1) * G].float().cpu().numpy()
+            want = oatt.decode_attention(qh, u.keys(), u.values())
+            err = np.max(np.abs(out[b, h * G:(h + 1) * G].cpu().numpy() - want))
+            assert err < attention_tol(u.values()), (t, b, h, err)
+    assert len(seen) > 1
 
 
 def test_window_partials_beyond_4gib():

@@ -304,8 +304,9 @@ def test_turbo_attention_workgroups_per_cu(batch, G):
 
 
 def test_turbo_attention_two_level_merge():
-    # batch 1, two kv-heads, 4096 tokens: partials merged in groups first
+    # batch 1, two kv-heads, 4500 tokens: partials merged in groups first
     bits = np.array([[[3, 2], [4, 3]]])
-    kvc, ks, vs, Rf = _build(workloads.BF16, 2, 4096, 64, bits, 1, G=8)
+    kvc, ks, vs, Rf = _build(workloads.BF16, 2, 4500, 64, bits, 1, G=8)
+    assert gh.split_plan(kvc.desc, 4500, 2).groups == 3
     units = _check(workloads.BF16, kvc, ks, vs, Rf, bits, 64, 1, 2)
     _attention(kvc, units, workloads.BF16, 1, 2, 8)
