@@ -68,44 +68,53 @@ __device__ __forceinline__ int slot(int t, int piece) {     // dword of the piec
   return t * kRow + 4 * (piece ^ (t & 7));
 }
 
-// The block's rows into LDS, the first 16 tokens by the first four of eight
-// copies; through registers where some lie in the window or the input is not
-// aligned to the copies' 16 bytes.
+// 32 consecutive rows into LDS, the first 16 tokens by the first four of eight
+// copies.  AUX: cache policy.
+template <int AUX>
+__device__ __forceinline__ void copy_rows(const uint16_t* rows, int lane, uint32_t* sm) {
+  const int g = lane >> 4, p = (lane & 15) ^ g;          // of token 4 j + g
+  const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(rows), 0, kChunk * kD * 2, 0x00020000);
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kRow * j), 16,
+                                             256 * g + 16 * (p ^ (j & 1 ? 4 : 0)), 1024 * j, 0,
+                                             AUX);
+}
+
+// The block's rows into LDS; through registers where they don't lie in one
+// piece (partly in the window, or in slots that wrap) or not at a multiple of
+// the copies' 16 bytes.
 __device__ __forceinline__ void stage_rows(const QuantLaunch& a, int b, int h, int kind, int t0,
                                            int lane, uint32_t* sm) {
   const uint16_t* in = (kind ? a.v : a.k) + (size_t)(b * a.H + h) * a.n_new * kD;
-  const int g = lane >> 4;
-  const int piece[2] = {(lane & 15) ^ g, (lane & 15) ^ g ^ 4};   // of token 4 j + g
   if (t0 >= a.n_past && lds_copy_aligned(in)) {          // the same for the wave
-    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(in + (size_t)(t0 - a.n_past) * kD), 0, kChunk * kD * 2, 0x00020000);
-    if (a.stream) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kRow * j), 16,
-                                                 256 * g + 16 * piece[j & 1], 1024 * j, 0, 2 /* NT */);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(sm + 4 * kRow * j), 16,
-                                                 256 * g + 16 * piece[j & 1], 1024 * j, 0, 0);
-    }
-  } else {
-    // the row's address selects between the new input and the window
-    const int cap = a.R + kChunk;
-    const uint16_t* ring = a.resid + (((size_t)b * a.H + h) * 2 + kind) * cap * kD;
-    u4 x[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int t = t0 + 4 * j + g;
-      const uint16_t* row = t >= a.n_past ? in + (size_t)(t - a.n_past) * kD
-                                          : ring + (size_t)(t % cap) * kD;
-      x[j] = gptr(reinterpret_cast<const u4*>(row))[piece[j & 1]];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      *reinterpret_cast<u4*>(sm + 4 * kRow * j + 4 * lane) = x[j];
+    in += (size_t)(t0 - a.n_past) * kD;
+    if (a.stream) copy_rows<2 /* NT */>(in, lane, sm);
+    else copy_rows<0>(in, lane, sm);
+    return;
   }
+  // (slots by one division: with one a row, eight a wave, and rows through
+  // registers a decode step's block, whose launch is one latency after
+  // another, took QuaRot 6.2 us, so 5.6, RTN 5.1 and 4.5, KIVI 5.5 and 4.9)
+  const int cap = a.R + kChunk, s0 = t0 % cap;
+  const uint16_t* ring = a.resid + (((size_t)b * a.H + h) * 2 + kind) * cap * kD;
+  const uint16_t* old = ring + (size_t)s0 * kD;
+  if (t0 + kChunk <= a.n_past && s0 + kChunk <= cap && lds_copy_aligned(old)) {
+    copy_rows<0>(old, lane, sm);
+    return;
+  }
+  u4 x[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int i = 4 * j + (lane >> 4), s = s0 + i;
+    const uint16_t* row = t0 + i >= a.n_past ? in + (size_t)(t0 + i - a.n_past) * kD
+                                             : ring + (size_t)(s < cap ? s : s - cap) * kD;
+    x[j] = gptr(reinterpret_cast<const u4*>(row))[(lane & 15) ^ (lane >> 4) ^ (j & 1 ? 4 : 0)];
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    *reinterpret_cast<u4*>(sm + 4 * kRow * j + 4 * lane) = x[j];
 }
 
 // Until at most N of the wave's copies are under way (the compiler does not
@@ -117,11 +126,16 @@ __device__ __forceinline__ void wait_rows() {
   asm volatile("" ::: "memory");
 }
 
+// The launch's window rows that any wave may copy.
+__device__ __forceinline__ void copy_any(const QuantLaunch& a, int lane) {
+  copy_window(a.ring, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
+              gridDim.x * gridDim.y * gridDim.z, lane);
+}
+
 // The launch's window rows (called when the wave's own rows are staged).
 __device__ __forceinline__ void copy_ring(const QuantLaunch& a, const BlockId& id, int lane) {
   if (a.ring_fused == kRingAny)
-    copy_window(a.ring, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
-                gridDim.x * gridDim.y * gridDim.z, lane);
+    copy_any(a, lane);
   else if (a.ring_fused == kRingFirst && id.blk == a.blk0)
     copy_unit_window(a.ring, id.b, id.h, id.kind, lane);
 }
@@ -582,6 +596,57 @@ __device__ __forceinline__ void sym_value_chunks(const uint32_t c[2][8], uint32_
   store_chunk<2 * B>(dst, w);
 }
 
+// The block's value chunks (first: its first channel's number in the region)
+// from the code bytes in LDS.
+__device__ __forceinline__ void sym_values(const uint32_t* sm, int bits, uint32_t* region,
+                                           size_t first, int lane) {
+  __builtin_amdgcn_wave_barrier();
+  // Lane -> the tokens of pass lane / 32 and channels 4 (lane % 32) .. + 3;
+  // after the exchange of the wave's halves, all tokens of two channels.
+  const int hf = lane >> 5, col = lane & 31;
+  uint32_t tr[4][4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    uint32_t r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int t = 4 * m + e;
+      r[e] = sm[hf * kSymCodes + t * (kD / 4) + (((t >> 1) & 1) ? col ^ 4 : col)];
+    }
+    const uint32_t a01 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u);
+    const uint32_t b01 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
+    const uint32_t a23 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u);
+    const uint32_t b23 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+    tr[0][m] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
+    tr[1][m] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
+    tr[2][m] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
+    tr[3][m] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
+  }
+  uint32_t c[2][8];
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const auto x = __builtin_amdgcn_permlane32_swap(tr[k][m], tr[2 + k][m], false, false);
+      c[k][m] = x[0];
+      c[k][4 + m] = x[1];
+    }
+  const size_t at = first + 4 * col + 2 * hf;
+#define RQ_CASE(NB) \
+  case NB: sym_value_chunks<NB>(c, region + at * NB); break;
+  switch (bits) {
+    RQ_CASE(2)
+    RQ_CASE(3)
+    RQ_CASE(4)
+    RQ_CASE(5)
+    RQ_CASE(6)
+    RQ_CASE(7)
+    RQ_CASE(8)
+    default: break;
+  }
+#undef RQ_CASE
+}
+
 template <int ROT, int BF16>
 __global__ void __launch_bounds__(kWave)
 sym_quant_kernel(QuantLaunch a) {
@@ -590,6 +655,11 @@ sym_quant_kernel(QuantLaunch a) {
   const int blk = id.blk, h = id.h, b = id.b, kind = id.kind;
   const int lane = threadIdx.x, tq = lane >> 2, q = lane & 3;
   const int nblk_cap = a.cap / kChunk, t0 = blk * kChunk;
+  // The launch's window rows, a latency of memory: before the rest in a
+  // decode step's wave (128 units, RTN 4.8 us with them behind, 4.6 so), else
+  // behind (1000 tokens, RTN 5.1 us with them in front, 4.9 so).
+  const bool ring_first = a.ring_fused == kRingAny && t0 < a.n_past;
+  if (ring_first) copy_any(a, lane);
   stage_rows(a, b, h, kind, t0, lane, sm);
   const int bits = kernarg_byte(&a.tab.bits[0][0], 2 * h + kind);
   const int off = 1 << (bits - 1);
@@ -659,7 +729,6 @@ sym_quant_kernel(QuantLaunch a) {
       }
     }
   }
-  copy_ring(a, id, lane);
   if (q == 0) {
     // tokens t and t + 16: a pair of the metadata's order
     uint32_t* m = reinterpret_cast<uint32_t*>(
@@ -667,52 +736,8 @@ sym_quant_kernel(QuantLaunch a) {
         (size_t)blk * kMetaBlockTok);
     __builtin_nontemporal_store(scale[0] | (scale[1] << 16), gptr(m) + tq);
   }
-  if (kind == 0) return;
-  __builtin_amdgcn_wave_barrier();
-  // Lane -> the tokens of pass lane / 32 and channels 4 (lane % 32) .. + 3;
-  // after the exchange of the wave's halves, all tokens of two channels.
-  const int hf = lane >> 5, col = lane & 31;
-  uint32_t tr[4][4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    uint32_t r[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int t = 4 * m + e;
-      r[e] = sm[hf * kSymCodes + t * (kD / 4) + (((t >> 1) & 1) ? col ^ 4 : col)];
-    }
-    const uint32_t a01 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u);
-    const uint32_t b01 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
-    const uint32_t a23 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u);
-    const uint32_t b23 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
-    tr[0][m] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
-    tr[1][m] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
-    tr[2][m] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
-    tr[3][m] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
-  }
-  uint32_t c[2][8];
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const auto x = __builtin_amdgcn_permlane32_swap(tr[k][m], tr[2 + k][m], false, false);
-      c[k][m] = x[0];
-      c[k][4 + m] = x[1];
-    }
-  const size_t at = ((size_t)b * nblk_cap + blk) * kD + 4 * col + 2 * hf;
-#define RQ_CASE(NB) \
-  case NB: sym_value_chunks<NB>(c, region + at * NB); break;
-  switch (bits) {
-    RQ_CASE(2)
-    RQ_CASE(3)
-    RQ_CASE(4)
-    RQ_CASE(5)
-    RQ_CASE(6)
-    RQ_CASE(7)
-    RQ_CASE(8)
-    default: break;
-  }
-#undef RQ_CASE
+  if (kind == 1) sym_values(sm, bits, region, ((size_t)b * nblk_cap + blk) * kD, lane);
+  if (!ring_first) copy_ring(a, id, lane);
 }
 
 __global__ void __launch_bounds__(kWave)
@@ -734,9 +759,13 @@ ring_kernel(RingLaunch a) {
 // the input, just written by the projections, is likely still in the 256 MiB
 // of last-level cache and plain loads find it there.  (RTN 4 bits, 8 kv-heads,
 // plain / non-temporal: 32 MiB 8.76 / 9.15 us, 64 MiB 15.5 / 16.6, 128 MiB
-// 31.7 / 30.5, 256 MiB 63.0 / 60.9, 512 MiB 123.3 / 119.0.)
+// 31.7 / 30.5, 256 MiB 63.0 / 60.9, 512 MiB 123.3 / 119.0; right after the
+// matrix products that write the input: RTN 4 bits 64 MiB 20.5 / 19.8, 96 MiB
+// 26.7 / 27.1, 192 MiB 47.8 / 42.8, KIVI 3 bits 27.1 / 28.1 and 52.5 / 46.9.
+// Only an input of 96 to 256 MiB that lies in that cache already, such as one
+// quantized again and again, is read faster by plain loads: 192 MiB, RTN 3
+// bits 36.6 / 45.2.)
 constexpr size_t kStreamBytes = (size_t)96 << 20;
-
 
 // Workgroups in order of the blocks of a unit, then the kv-heads and kinds of
 // a batch entry (the inputs' order), or, for units of at least 6144 tokens,

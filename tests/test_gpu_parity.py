@@ -577,11 +577,12 @@ def test_large_launch_equals_small_ones(family):
 
 @pytest.mark.parametrize("family", [workloads.KIVI, workloads.QUAROT, workloads.RTN,
                                     workloads.KIVI_RTN])
-@pytest.mark.parametrize("R", [0, 32, 96])
+@pytest.mark.parametrize("R", [0, 32, 40, 96])
 def test_chunked_window_copies(family, R):
     """Chunks whose window rows take ring slots that no block, one block or
     several blocks of the same append still read, with one and many blocks a
-    unit, against the oracle on all tokens."""
+    unit, whose rows lie in the new input, in the window, in both (R = 0) or in
+    slots that wrap (R = 40), against the oracle on all tokens."""
     torch = _torch()
     B, H, dtype = 2, 3, workloads.F16
     chunks = [32, 64, 64, 32, 33, 63, 100, 31, 1, 224, 7, 65, 128]
