@@ -3,16 +3,16 @@
 //
 // Flat grid of (workgroup slot, unit) with the unit fastest, four waves per
 // workgroup; a unit is one (batch, kv-head).  Slots 0 .. nwg[h]-1 stream the
-// quantized 32-token blocks of their unit (about three workgroups per CU in
-// all, each kv-head's share sized by the cost of its widths); the first
-// slots first attend to the 16-bit residual window, 32 tokens each (or, where
-// the chip has room for them, workgroups of their own do).  Each workgroup
-// writes a partial (max, sum, acc) with cache-coherent stores and takes a
-// ticket from a per-unit counter; the last to arrive merges the unit's
-// partials and writes the output (QuaRot: rotated back).  A wave streams every
-// fourth block of its slot's range: the block's bytes (codes and metadata)
-// are fetched two blocks ahead with 1 KB-per-instruction loads and copied
-// into the wave's LDS slot, from where each lane reads its MFMA operands.
+// quantized 32-token blocks of their unit (two or three workgroups per CU in
+// all, as many for every unit); the first slots first attend to the 16-bit
+// residual window, 32 tokens each (or, where the chip has room for them,
+// workgroups of their own do).  Each workgroup writes a partial (max, sum,
+// acc) with cache-coherent stores and takes a ticket from a per-unit counter;
+// the last to arrive merges the unit's partials and writes the output (QuaRot:
+// rotated back), in two levels where the slots are many.  A wave streams its
+// first blocks from fixed places and claims the others one by one: a block's
+// bytes (codes and metadata) are copied straight to a ring of two to four LDS
+// slots, 1 KB an instruction, from where each lane reads its MFMA operands.
 //
 // Per block (32 tokens) a wave runs QK^T and PV on v_mfma_f32_16x16x32_f16.
 // The VALU only turns packed fields into fp16 operands: a b-bit field masked
@@ -1771,7 +1771,8 @@ __device__ __forceinline__ void stream_slot(const AttnLaunch& a, int slot, int n
 // nwin window slots behind them (original domain).  dst: a partial slot to
 // write the merged (max, sum, acc) to, or -1 to write the unit's output.  Thread t owns E consecutive elements of one query row (128 G / E
 // <= 256); up to kS slots are loaded at once, the
-// missing ones as zeros, so that a merge of up to 16 slots is one latency.
+// missing ones as zeros, so that a merge of up to 16 slots (8 for more than
+// eight queries) is one latency.
 // Whole workgroup; lds: scratch of 128 G floats, plus the rotation
 // (TurboQuant, 32 KB).
 template <int E>
@@ -1945,11 +1946,11 @@ __global__ void __launch_bounds__(kThreads, kAttnOcc) __attribute__((amdgpu_num_
 attn_kernel(AttnLaunch a) {
   __shared__ u4 cst4[2];             // fp16 ones (4 dwords), zeros (4 dwords)
   uint32_t* cst = reinterpret_cast<uint32_t*>(cst4);
-  // one area used in turn for the waves' block rings while streaming and
-  // the wave merge area [kWaves][G][2 + 128] floats (window workgroups:
-  // staging, then their scaled query rows); behind it the G 16-bit query
-  // rows (uint16 [G][128]) and, for TurboQuant, the G rotated rows (float
-  // [G][128])
+  // one area used in turn for a window chunk's probabilities (2 KiB of each
+  // wave's ring), the waves' block rings while streaming, the wave merge area
+  // [kWaves][G][2 + 128] floats and the scratch of the merging workgroup;
+  // behind it the G 16-bit query rows (uint16 [G][128]) and, for TurboQuant,
+  // the G rotated rows (float [G][128]) and the code tables
   extern __shared__ u4 dyn[];
   uint8_t* slots = reinterpret_cast<uint8_t*>(dyn);
   float* merge = reinterpret_cast<float*>(dyn);

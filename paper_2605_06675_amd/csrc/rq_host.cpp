@@ -296,7 +296,7 @@ int claim_offset(const rq_cache* c) { return 16 * ((1 + max_groups(c) + 15) / 16
 int counter_stride(const rq_cache* c) { return claim_offset(c) + 16 * max_groups(c); }
 
 // Workspace: per-unit arrival and claim counters, padded to 256 bytes, then
-// the partials [B][H][n_wg + n_rw + groups][G][2 + 128] floats.
+// the partials [B][H][nwg + groups + n_rw][G][2 + 128] floats.
 uint64_t attn_counter_bytes(const rq_cache* c) {
   return ((uint64_t)c->batch * c->n_kv_heads * counter_stride(c) * sizeof(uint64_t) + 255) /
          256 * 256;
@@ -569,7 +569,7 @@ rq_status rq_decode_workspace(const rq_cache* c, int32_t n_tokens,
   if (n_tokens < 1 || n_tokens > c->capacity)
     return fail(RQ_EINVAL, "n_tokens %d outside 1..%d", n_tokens, c->capacity);
   if (!bytes) return fail(RQ_EINVAL, "bytes is NULL");
-  // the largest over the layers (their kv-heads share the grid by cost)
+  // the largest over the layers
   uint64_t most = 0;
   for (int l = 0; l < c->n_layers; ++l) {
     const uint64_t b = attn_ws_bytes(c, plan_splits(c, l, n_tokens));

@@ -117,12 +117,13 @@ struct AttnLaunch {
   int B, H, G, cap, R;
   int GP;                 // smallest power of two >= G (KIVI keys: at least 4)
   int nq, n_tokens;
-  int n_wg;               // grid slots per unit: the largest nwg[h]
+  int n_wg;               // grid slots per unit: the largest nwg[h], and
+                          // n_rw more where win_wg
   uint16_t nwg[RQ_MAX_KV_HEADS];  // workgroups streaming blocks, per kv-head
   int n_rw;               // chunks of the 16-bit window (kAttnResChunk tokens)
   int win_wg;             // 1: each chunk has a workgroup of its own
   int wave_bytes;         // LDS bytes of one wave's block ring
-  int area_bytes;         // LDS bytes of the ring/merge/staging area
+  int area_bytes;         // LDS bytes of the window/ring/merge area
   int is_bf16, family;
   float qscale;           // scale * log2(e)
   // The window's scores are (2^wexp q) . k times wscale = qscale 2^-wexp.
@@ -153,8 +154,8 @@ hipError_t launch_quantize_turbo(const QuantLaunch& a, hipStream_t s);
 hipError_t launch_ring(const RingLaunch& a, hipStream_t s);
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
 // LDS of the attention kernel: the area (the waves' block rings while
-// streaming; the wave merge, window staging and merging scratch after or
-// instead), then the 16-bit query rows and, for TurboQuant, the rotated
+// streaming; a window chunk's probabilities before, the wave merge and the
+// merging scratch after), then the 16-bit query rows and, for TurboQuant, the rotated
 // query rows.  attention_area_bytes: the area for rings of wave_bytes each.
 size_t attention_area_bytes(int G, int wave_bytes, int family);
 size_t attention_lds_bytes(int G, int wave_bytes, int family);

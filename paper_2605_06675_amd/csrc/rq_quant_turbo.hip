@@ -23,7 +23,7 @@
 // (4 x 8 units of 32768 tokens, 2..4 bits at 3.0): 207 us before, 149 us
 // now; at 5.25 bits on average (a count of 2 P comparisons before) 260 us
 // and 93 us for 4 x 8 x 15584 tokens.  Four workgroups a CU without a
-// second register buffer (118 registers) beat three with one (149 and 157
+// second register buffer (112 registers) beat three with one (149 and 157
 // us): the other waves' work covers the loads.
 #include "rq_device.h"
 #include "rq_internal.h"
@@ -202,8 +202,8 @@ __device__ __forceinline__ uint32_t norm_of(const u4* x) {
 // turned into codes together (codes_of_fields).  The sign is t's sign bit,
 // and t = 0 (a zero coordinate, a token of norm zero) belongs to the
 // negative side: t is formed by a fused multiply-add of -2^-149, fp32's
-// least subnormal, which leaves every other rounded product as it is (a product
-// halfway between two fp32 values may round the other way).
+// least subnormal, which leaves every other rounded product as it is (but for
+// one halfway between two fp32 values, which may round the other way).
 //
 // Widths 1..3: the bits of a field are compared one by one (bisection over
 // th) and shifted into the quarter's dword, one add with carry per bit, so
