@@ -210,8 +210,11 @@ struct AttnShape {
 // 8192 26.0 / 25.5, 96 x 2048 22.6 / 20.4).
 // Wider layers and the other families lose (TurboQuant to 6 bits, 8 units of
 // 97088 tokens 52.6 / 50.2; KIVI, 128 units of 8192 36.2 / 33.4).
+bool may_take_two(const rq_cache* c, int max_bits) {
+  return c->family == RQ_TURBO && max_bits <= 4;
+}
 bool two_per_cu(const rq_cache* c, int max_bits, int n_tokens) {
-  if (c->family != RQ_TURBO || max_bits > 4) return false;
+  if (!may_take_two(c, max_bits)) return false;
   const long units = (long)c->batch * c->n_kv_heads, cus = cu_count();
   const long nblk = n_quantized(n_tokens, c->residual) / rq::kChunk, most = (nblk + 3) / 4;
   const bool fills = 2 * cus % units == 0, few = c->n_q_heads <= 2 * c->n_kv_heads;
@@ -368,13 +371,20 @@ rq_status decode_attention(const rq_cache* c, int32_t layer, int32_t n_tokens, c
     }
   }
   AttnShape shape;
-  if (!attn_shape(c, max_blk, two_per_cu(c, max_bits, n_tokens), &shape))
-    return fail(RQ_EUNSUPPORTED,
-                "layer %d: two %d-byte blocks per wave do not fit the LDS of a CU "
-                "(K+V bit-widths of one kv-head are too wide)", layer, max_blk);
-  const SplitPlan p = plan_splits(c, layer, n_tokens, shape.wg_per_cu);
+  SplitPlan p;
   const uint64_t need_c = attn_counter_bytes(c);
-  const uint64_t need_p = attn_ws_bytes(c, p) - need_c;
+  uint64_t need_p;
+  // (a layer that may take two a CU does so where the partials of three do not
+  // fit)
+  for (bool two = two_per_cu(c, max_bits, n_tokens);; two = true) {
+    if (!attn_shape(c, max_blk, two, &shape))
+      return fail(RQ_EUNSUPPORTED,
+                  "layer %d: two %d-byte blocks per wave do not fit the LDS of a CU "
+                  "(K+V bit-widths of one kv-head are too wide)", layer, max_blk);
+    p = plan_splits(c, layer, n_tokens, shape.wg_per_cu);
+    need_p = attn_ws_bytes(c, p) - need_c;
+    if (two || need_p <= part_cap || !may_take_two(c, max_bits)) break;
+  }
   if (counter_cap < need_c || part_cap < need_p)
     return fail(RQ_ESMALLWS, "workspace: counters %llu of %llu bytes, partials %llu of %llu",
                 (unsigned long long)counter_cap, (unsigned long long)need_c,

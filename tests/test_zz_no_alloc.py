@@ -61,3 +61,29 @@ def test_static_scratch_rejects_oversized_partials():
     with pytest.raises(rq.RQError) as e:
         kvc.attention_static(0, q, out)
     assert e.value.status == rq.RQ_ESMALLWS
+
+
+def test_static_scratch_takes_fewer_workgroups():
+    # TurboQuant, 192 units, a window of 7 chunks: the partials of three
+    # workgroups a CU exceed the scratch, those of two fit
+    import torch
+    from tests import test_gpu_turbo as gt
+    B, H, G, T, R = 24, 8, 8, 2000, 200
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K, V = (torch.randn((B, H, T, 128), generator=g, device="cuda").to(torch.bfloat16)
+            for _ in range(2))
+    q = torch.randn((B, H * G, 128), generator=g, device="cuda").to(torch.bfloat16)
+    r16, _ = gt._rotations(1, H)
+    kvc = rq.KVCache(rq.RQ_TURBO, rq.RQ_BF16, 1, B, H, H * G, 2016, R,
+                     np.array([[[2 + h % 3, 3] for h in range(H)]]),
+                     rotation=gh.dev(r16, workloads.BF16))
+    kvc.append(0, K, V)
+    slots = [p.workgroups + p.chunks + p.groups
+             for p in (gh.split_plan(kvc.desc, T, n) for n in (2, 3))]
+    two, three = (B * H * n * G * 130 * 4 for n in slots)
+    assert two <= rq.lib().rq_decode_static_bytes() - (1 << 20) < three
+    ref = kvc.attention(0, q)
+    out = torch.full_like(ref, float("nan"))
+    kvc.attention_static(0, q, out)
+    torch.cuda.synchronize()
+    assert float((out - ref).abs().max()) < gp.ATOL
