@@ -593,7 +593,7 @@ def test_chunked_window_copies(family, R):
 
 
 @pytest.mark.parametrize("B,H,R", [(1, 4, 32), (1, 4, 64), (1, 8, 96), (8, 8, 96)])
-@pytest.mark.parametrize("family", [workloads.KIVI, workloads.RTN])
+@pytest.mark.parametrize("family", [workloads.KIVI, workloads.RTN, workloads.KIVI_RTN])
 def test_long_append_to_a_few_tokens(family, B, H, R):
     """A window that 20 tokens begin to fill and one append fills and passes:
     its rows copied by the waves of the first blocks (few rows, or many such
